@@ -37,8 +37,8 @@
 // transfers (no staging registers).  Rows past the end of a context or query
 // range are zero-filled and add nothing to any gradient.
 //
-// fp32 path (correctness path for fp32 plans): one lane per query (dQ) or
-// per context key (dK, dV), plain fp32 arithmetic with expf.
+// fp32 plans take the dQ, dK and dV kernels of attention_f32.hip; the rowsum
+// and scatter kernels here serve both.
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
@@ -645,88 +645,6 @@ void dkdv_kernel(BwdArgs a) {
   }
 }
 
-// ------------------------------------------------------------------ fp32 path
-
-template <int D>
-__global__ __launch_bounds__(kBwdF32) void dq_f32_kernel(BwdArgs a) {
-  int g = 0;
-  while (g + 1 < a.n_groups && static_cast<int>(blockIdx.x) >= a.groups[g + 1].dq_block_begin) ++g;
-  const BwdGroupArgs& G = a.groups[g];
-  const int idx = blockIdx.x - G.dq_block_begin;
-  const int head = idx / G.n_qblocks, qt = idx % G.n_qblocks;
-  const int q_row = G.q_begin + qt * kBwdF32 + threadIdx.x;
-  if (q_row >= G.q_end) return;
-  const int64_t ld = a.ld, hoff = static_cast<int64_t>(head) * D;
-  const float* qp = static_cast<const float*>(a.q) + static_cast<int64_t>(q_row) * ld + hoff;
-  const float* gp = static_cast<const float*>(a.d_out) + static_cast<int64_t>(q_row) * ld + hoff;
-  const int64_t stat = static_cast<int64_t>(head) * a.n_q + q_row;
-  const float lse = a.lse[stat], dsum = -a.dsum[stat];
-  float acc[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) acc[d] = 0.f;
-  for (int j = 0; j < G.n_kv; ++j) {
-    const float* kp = ctx_row<float>(G, j, false, ld) + hoff;
-    const float* vp = ctx_row<float>(G, j, true, ld) + hoff;
-    float s = 0.f, dp = 0.f;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      s = __builtin_fmaf(qp[d], kp[d], s);
-      dp = __builtin_fmaf(gp[d], vp[d], dp);
-    }
-    const float ds = expf(s * a.scale - lse) * (dp - dsum);
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = __builtin_fmaf(ds, kp[d], acc[d]);
-  }
-  float* op = static_cast<float*>(a.dq) + static_cast<int64_t>(q_row) * ld + hoff;
-#pragma unroll
-  for (int d = 0; d < D; ++d) op[d] = acc[d] * a.scale;
-}
-
-template <int D>
-__global__ __launch_bounds__(kBwdF32) void dkdv_f32_kernel(BwdArgs a) {
-  int g = 0;
-  while (g + 1 < a.n_groups && static_cast<int>(blockIdx.x) >= a.groups[g + 1].kv_block_begin) ++g;
-  const BwdGroupArgs& G = a.groups[g];
-  const int idx = blockIdx.x - G.kv_block_begin;
-  const int head = idx / G.n_kblocks, kt = idx % G.n_kblocks;
-  const int key = kt * kBwdF32 + threadIdx.x;
-  if (key >= G.n_kv) return;
-  const int64_t ld = a.ld, hoff = static_cast<int64_t>(head) * D;
-  const float* kp = ctx_row<float>(G, key, false, ld) + hoff;
-  const float* vp = ctx_row<float>(G, key, true, ld) + hoff;
-  float dk[D], dv[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    dk[d] = 0.f;
-    dv[d] = 0.f;
-  }
-  for (int q = G.q_begin; q < G.q_end; ++q) {
-    const float* qp = static_cast<const float*>(a.q) + static_cast<int64_t>(q) * ld + hoff;
-    const float* gp = static_cast<const float*>(a.d_out) + static_cast<int64_t>(q) * ld + hoff;
-    const int64_t stat = static_cast<int64_t>(head) * a.n_q + q;
-    float s = 0.f, dp = 0.f;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      s = __builtin_fmaf(qp[d], kp[d], s);
-      dp = __builtin_fmaf(gp[d], vp[d], dp);
-    }
-    const float p = expf(s * a.scale - a.lse[stat]);
-    const float ds = p * (dp + a.dsum[stat]);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      dv[d] = __builtin_fmaf(p, gp[d], dv[d]);
-      dk[d] = __builtin_fmaf(ds, qp[d], dk[d]);
-    }
-  }
-  float* dkp = G.dk_ctx + static_cast<int64_t>(key) * ld + hoff;
-  float* dvp = G.dv_ctx + static_cast<int64_t>(key) * ld + hoff;
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    dkp[d] = dk[d] * a.scale;
-    dvp[d] = dv[d];
-  }
-}
-
 // ------------------------------------------------------------------ scatter to the sources
 
 // One thread per 16-byte output chunk of a source token; it adds, in group
@@ -793,38 +711,25 @@ hipError_t launch_bwd_dot(const DotArgs& a, bool bf16, hipStream_t stream) {
 
 hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_dim, bool bf16,
                       hipStream_t stream) {
-  // dK/dV first: for bf16 plans it writes the dS tiles the dQ kernel reads.
+  if (!bf16) return launch_bwd_f32(a, dq_blocks, kv_blocks, head_dim, stream);
+  // dK/dV first: it writes the dS tiles the dQ kernel reads.
   if (kv_blocks > 0) {
-    if (bf16) {
-      if (head_dim == 128 && a.q_prescaled)
-        hipLaunchKernelGGL((dkdv_kernel<128, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
-      else if (head_dim == 128)
-        hipLaunchKernelGGL((dkdv_kernel<128, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
-      else if (a.q_prescaled)
-        hipLaunchKernelGGL((dkdv_kernel<64, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
-      else
-        hipLaunchKernelGGL((dkdv_kernel<64, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
-    } else {
-      if (head_dim == 128)
-        hipLaunchKernelGGL(dkdv_f32_kernel<128>, dim3(kv_blocks), dim3(kBwdF32), 0, stream, a);
-      else
-        hipLaunchKernelGGL(dkdv_f32_kernel<64>, dim3(kv_blocks), dim3(kBwdF32), 0, stream, a);
-    }
+    if (head_dim == 128 && a.q_prescaled)
+      hipLaunchKernelGGL((dkdv_kernel<128, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+    else if (head_dim == 128)
+      hipLaunchKernelGGL((dkdv_kernel<128, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+    else if (a.q_prescaled)
+      hipLaunchKernelGGL((dkdv_kernel<64, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+    else
+      hipLaunchKernelGGL((dkdv_kernel<64, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (dq_blocks > 0) {
-    if (bf16) {
-      if (head_dim == 128)
-        hipLaunchKernelGGL(dq_kernel<128>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
-      else
-        hipLaunchKernelGGL(dq_kernel<64>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
-    } else {
-      if (head_dim == 128)
-        hipLaunchKernelGGL(dq_f32_kernel<128>, dim3(dq_blocks), dim3(kBwdF32), 0, stream, a);
-      else
-        hipLaunchKernelGGL(dq_f32_kernel<64>, dim3(dq_blocks), dim3(kBwdF32), 0, stream, a);
-    }
+    if (head_dim == 128)
+      hipLaunchKernelGGL(dq_kernel<128>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
+    else
+      hipLaunchKernelGGL(dq_kernel<64>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
     return hipGetLastError();
   }
   return hipSuccess;

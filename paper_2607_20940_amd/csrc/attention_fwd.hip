@@ -24,10 +24,9 @@
 // that every SIMD always has one wave feeding its matrix core.
 // Keys past the end of a run are zero-filled in LDS and masked to -inf.
 //
-// fp32 path: one lane per query, plain fp32 FMA dot products and an online
-// softmax with expf; used for fp32 plans (correctness path).
+// fp32 plans take the kernels of attention_f32.hip.
 //
-// Optionally (a.lse non-null) every path also writes, per head and query, the
+// Optionally (a.lse non-null) the kernels also write, per head and query, the
 // natural log of the softmax denominator, log sum_j exp(scale q k_j): the
 // statistic the backward pass recomputes the probabilities from.
 #include <hip/hip_runtime.h>
@@ -47,20 +46,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-
-// Logical block -> (group, head, query tile).  Groups are stored longest
-// context first; inside a group consecutive blocks share a head.
-struct Work {
-  int g, head, tile;
-};
-
-__device__ inline Work decode(const FwdArgs& a, int L) {
-  int g = 0;
-  while (g + 1 < a.n_groups && L >= a.groups[g + 1].block_begin) ++g;
-  const int idx = L - a.groups[g].block_begin;
-  const int nt = a.groups[g].n_qtiles;
-  return {g, idx / nt, idx % nt};
-}
 
 // Lazy rescaling threshold (log2 units): the running max used for the
 // exponentials is raised only when a tile's max exceeds it by more than this,
@@ -709,51 +694,6 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
                              static_cast<int64_t>(head) * D + 4 * d4) = v;
 }
 
-template <int D>
-__global__ __launch_bounds__(kFwdF32BM) void fwd_f32_kernel(FwdArgs a) {
-  const Work w = decode(a, blockIdx.x);
-  const FwdGroupArgs& G = a.groups[w.g];
-  const int q_row = G.q_begin + w.tile * kFwdF32BM + threadIdx.x;
-  if (q_row >= G.q_end) return;
-  const int64_t ld = a.ld;
-  const int64_t hoff = static_cast<int64_t>(w.head) * D;
-  const float* qp = static_cast<const float*>(a.q) + static_cast<int64_t>(q_row) * ld + hoff;
-  float q[D], o[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    q[d] = qp[d];
-    o[d] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  for (int r = 0; r < G.n_runs; ++r) {
-    const float* Kg = static_cast<const float*>(G.runs[r].k) + hoff;
-    const float* Vg = static_cast<const float*>(G.runs[r].v) + hoff;
-    for (int j = 0; j < G.runs[r].n_tok; ++j) {
-      const float* kp = Kg + static_cast<int64_t>(j) * ld;
-      const float* vp = Vg + static_cast<int64_t>(j) * ld;
-      float dot = 0.f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) dot = __builtin_fmaf(q[d], kp[d], dot);
-      const float z = dot * a.scale;
-      if (z > m) {
-        const float alpha = expf(m - z);
-        l *= alpha;
-#pragma unroll
-        for (int d = 0; d < D; ++d) o[d] *= alpha;
-        m = z;
-      }
-      const float p = expf(z - m);
-      l += p;
-#pragma unroll
-      for (int d = 0; d < D; ++d) o[d] = __builtin_fmaf(p, vp[d], o[d]);
-    }
-  }
-  float* op = static_cast<float*>(a.out) + static_cast<int64_t>(q_row) * ld + hoff;
-#pragma unroll
-  for (int d = 0; d < D; ++d) op[d] = o[d] / l;
-  if (a.lse) a.lse[static_cast<int64_t>(w.head) * a.n_q + q_row] = m + logf(l);
-}
-
 }  // namespace
 
 hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t stream) {
@@ -775,12 +715,7 @@ hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t
       hipLaunchKernelGGL(combine_kernel<64>, dim3(a.n_ranges - 1, kFwdBM * 64 / 4 / kCombineThreads), dim3(kCombineThreads), 0, stream, a);
     return hipGetLastError();
   }
-  if (a.n_blocks <= 0) return hipSuccess;
-  if (head_dim == 128)
-    hipLaunchKernelGGL(fwd_f32_kernel<128>, dim3(a.n_blocks), dim3(kFwdF32BM), 0, stream, a);
-  else
-    hipLaunchKernelGGL(fwd_f32_kernel<64>, dim3(a.n_blocks), dim3(kFwdF32BM), 0, stream, a);
-  return hipGetLastError();
+  return launch_forward_f32(a, head_dim, stream);
 }
 
 int forward_blocks_per_cu(int head_dim) {

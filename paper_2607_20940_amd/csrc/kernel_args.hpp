@@ -17,8 +17,11 @@ constexpr int kFwdBN = 64;
 constexpr int kFwdThreads = 512;
 // Merge of split items: threads per block (one output float4 each).
 constexpr int kCombineThreads = 256;
-// fp32 attention kernel: one query per lane, one wave per block.
-constexpr int kFwdF32BM = 64;
+// Kernels whose eight waves split the context of 32 queries (fp32 forward):
+// queries per item, threads per block.
+constexpr int kFwdF32BM = 32;
+constexpr int kSplitWaves = 8;
+constexpr int kSplitThreads = 64 * kSplitWaves;
 
 constexpr int kPoolThreads = 256;
 
@@ -52,8 +55,8 @@ struct FwdArgs {
   int64_t total_tiles;      // bf16 kernel: tiles of all (group, head, query tile) items
   int64_t tail_begin;       // bf16 kernel: first tile after the whole-item rounds
   int32_t dp_rounds;        // bf16 kernel: rounds of whole items before the tail ranges
-  int32_t pad2;
-  float* partial;           // bf16 kernel: 2 * n_ranges partial records
+  int32_t key_splits;       // fp32 kernel: blocks that share the context of one item
+  float* partial;           // bf16 kernel: 2 * n_ranges partial records; key_splits > 1: a record per item and split
   int64_t* range_table;     // bf16 kernel: first tile of each tail range (n_ranges + 1), written by the attention kernel
   float* lse;               // optional [heads, n_q]: log of the softmax denominator (natural log)
   int32_t n_q;
@@ -64,6 +67,10 @@ struct FwdArgs {
 // One partial record: unnormalised O [BM][D] (fp32), running max m [BM] and
 // row sum l [BM] of one piece of an item that spans several tile ranges.
 constexpr int64_t partial_record_floats(int head_dim) { return static_cast<int64_t>(kFwdBM) * (head_dim + 2); }
+
+// One record of an item whose context is split over key_splits blocks: O
+// [32][D] (fp32, unnormalised), m [32] and l [32].
+constexpr int64_t split_record_floats(int head_dim) { return 32 * static_cast<int64_t>(head_dim + 2); }
 
 // ---------------------------------------------------------------- backward
 
@@ -77,7 +84,7 @@ constexpr int kBwdK = 128;     // dK/dV kernel: keys per block (4 wave pairs x 3
 constexpr int kBwdKVThreads = 512;  // dK/dV kernel: 8 waves, two per SIMD
 constexpr int kBwdQS = 64;     // dK/dV kernel: queries per LDS stage
 constexpr int64_t kBwdDsBudget = int64_t(8) << 30;  // bytes of dS tiles held at once (whole heads, at least one)
-constexpr int kBwdF32 = 64;    // fp32 kernels: one query or key per lane
+constexpr int kBwdF32 = 32;    // fp32 kernels: queries (dQ) or keys (dK, dV) per block
 constexpr int kDotThreads = 256;
 constexpr int kMaxScatterJobs = 10;
 

@@ -11,16 +11,19 @@ namespace mssa {
 hipError_t launch_pool(const PoolArgs& a, int n_blocks, bool bf16, hipStream_t stream);
 
 // Attention forward over the groups of `a`.  bf16: a.n_ranges persistent
-// blocks followed by the combine of split items; fp32: a.n_blocks blocks.
+// blocks followed by the combine of split items; fp32: a.n_blocks items, each
+// over a.key_splits blocks, followed by their combine.
 hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t stream);
+hipError_t launch_forward_f32(const FwdArgs& a, int head_dim, hipStream_t stream);  // its fp32 half
 
 // Backward: rowsum(d_out * out) per head and query.
 hipError_t launch_bwd_dot(const DotArgs& a, bool bf16, hipStream_t stream);
 
 // Backward: dQ kernel (dq_blocks blocks), then dK/dV context gradients
-// (kv_blocks blocks).
+// (kv_blocks blocks); fp32 plans run both in one launch.
 hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_dim, bool bf16,
                       hipStream_t stream);
+hipError_t launch_bwd_f32(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_dim, hipStream_t stream);
 
 // Backward: context gradients to the sink, history and window tokens; grid
 // (n_blocks, 2): y = 0 for K, y = 1 for V.

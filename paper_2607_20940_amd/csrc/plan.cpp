@@ -262,6 +262,28 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     p.partial_bytes = rec_bytes + align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
     ws += p.partial_bytes;
   }
+  if (d.dtype == MSSA_F32) {
+    // The eight waves of a block take 32-key tiles in turn; a context is
+    // split over several blocks while that leaves every wave a tile and the
+    // items alone leave CUs idle.
+    int64_t items = 0, tiles = 0;
+    for (int g = 0; g < G; ++g) {
+      items += static_cast<int64_t>((p.groups[g].q_end - p.groups[g].q_begin + kFwdF32BM - 1) / kFwdF32BM) * d.num_heads;
+      int64_t t = 0;
+      for (const Run& r : p.runs[g]) t += (r.n_tok + 31) / 32;
+      tiles = std::max(tiles, t);
+    }
+    const int64_t s = std::max<int64_t>(1, std::min(slots / items, (tiles + kSplitWaves - 1) / kSplitWaves));
+    const int64_t bytes = align256(items * s * split_record_floats(d.head_dim) * 4);
+    // never so large that the entry point without allocations, which took
+    // the plan without records, would refuse it
+    if (s > 1 && (ws + bytes <= MSSA_NOALLOC_SCRATCH_BYTES || ws > MSSA_NOALLOC_SCRATCH_BYTES)) {
+      p.key_splits = static_cast<int32_t>(s);
+      p.partial_off = ws;
+      p.partial_bytes = bytes;
+      ws += bytes;
+    }
+  }
   p.workspace_bytes = ws;
 
   // Backward workspace and the scatter of context gradients to the sources.

@@ -1,0 +1,46 @@
+"""Small layers at the edges of the kernels whose waves split the context of a
+32-query item: one query more or less than a tile, contexts of one key, of
+fewer tiles than waves and of many, split over several blocks or not; forward,
+log-sum-exp and every gradient against the fp64 oracle.
+
+Tolerances as for the other parity tests (tolerances.py, test_gpu_backward):
+fp32 sums of a few thousand terms in any order stay near 1e-6 relative."""
+
+import numpy as np
+import pytest
+
+from gpu_common import assert_close
+from test_gpu_backward import BwdRun, _assert_grads, _desc
+
+pytestmark = pytest.mark.gpu
+
+# (scales, grid, frames, sink, hist, heads): 32 and 33 queries per scale; a
+# single query on a context of one key; runs of 31 and 1 tokens; one head on a
+# long history (split over blocks); several heads, no split.
+SHAPES = {
+    "one_token": ([1], (1, 1), 1, 0, 0, 1),
+    "tile_32": ([1], (4, 8), 1, 0, 1, 1),
+    "tile_33": ([1, 2], (3, 11), 1, 1, 0, 2),
+    "run_31": ([1, 1], (1, 31), 1, 1, 1, 1),
+    "long_history": ([1, 2], (5, 7), 1, 1, 40, 1),
+    "many_items": ([1, 2, 4], (11, 13), 2, 1, 3, 12),
+}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_fp32_layer(name, d):
+    scales, (h, w), f, s, hist, nh = SHAPES[name]
+    print(f"[small] f32 {name} d={d}", flush=True)
+    desc = _desc(len(scales), scales, h, w, F=f, S=s, Hh=hist, nh=nh, d=d)
+    r = BwdRun(desc, "f32", 40 + d, 1.0 / np.sqrt(d))
+    r.run()
+    x = r.x64()
+    import oracle
+    ref = oracle.mssa_attention(desc, x["q_win"], x["k_sink"], x["v_sink"], x["k_hist"], x["v_hist"], x["k_win"],
+                                x["v_win"])
+    assert_close(r.out.cpu().numpy().astype(np.float64), ref, "f32", name)
+    lse = r.lse.cpu().numpy().reshape(nh, -1).astype(np.float64)
+    assert np.abs(lse - r.oracle_lse()).max() <= 1e-5, name
+    if name != "one_token":  # a single key: dq and dk are exactly zero, and so is their reference
+        _assert_grads(r.grads(), r.oracle(), "f32", name)
