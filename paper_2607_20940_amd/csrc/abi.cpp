@@ -372,7 +372,7 @@ mssa_status forward_launch(const mssa::Plan& p, const GroupRuns& runs, const mss
   a.key_splits = p.key_splits;
   const char* ws = static_cast<const char*>(workspace);
   a.partial = p.partial_bytes > 0 ? reinterpret_cast<float*>(const_cast<char*>(ws) + p.partial_off) : nullptr;
-  a.range_table = bf16 && p.partial_bytes > 0 ? reinterpret_cast<int64_t*>(const_cast<char*>(ws) + p.range_table_off) : nullptr;
+  a.range_table = bf16 && p.n_ranges > 1 ? reinterpret_cast<int64_t*>(const_cast<char*>(ws) + p.range_table_off) : nullptr;
   int64_t blocks = 0;
   int gi = 0;
   for (int g : p.order) {

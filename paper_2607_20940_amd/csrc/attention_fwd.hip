@@ -697,6 +697,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
 }  // namespace
 
 hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t stream) {
+  if (bf16 && a.key_splits > 0) return launch_forward_small(a, head_dim, stream);
   if (bf16) {
     if (a.n_ranges <= 0) return hipSuccess;
     if (head_dim == 128 && a.q_prescaled)

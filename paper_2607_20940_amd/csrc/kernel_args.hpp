@@ -17,8 +17,8 @@ constexpr int kFwdBN = 64;
 constexpr int kFwdThreads = 512;
 // Merge of split items: threads per block (one output float4 each).
 constexpr int kCombineThreads = 256;
-// Kernels whose eight waves split the context of 32 queries (fp32 forward):
-// queries per item, threads per block.
+// Kernels whose eight waves split the context of 32 queries (fp32 plans, and
+// the bf16 forward of small layers): queries per item, waves per block.
 constexpr int kFwdF32BM = 32;
 constexpr int kSplitWaves = 8;
 constexpr int kSplitThreads = 64 * kSplitWaves;
@@ -55,7 +55,7 @@ struct FwdArgs {
   int64_t total_tiles;      // bf16 kernel: tiles of all (group, head, query tile) items
   int64_t tail_begin;       // bf16 kernel: first tile after the whole-item rounds
   int32_t dp_rounds;        // bf16 kernel: rounds of whole items before the tail ranges
-  int32_t key_splits;       // fp32 kernel: blocks that share the context of one item
+  int32_t key_splits;       // 32-query items (fp32; bf16 if > 0): blocks that share an item's context
   float* partial;           // bf16 kernel: 2 * n_ranges partial records; key_splits > 1: a record per item and split
   int64_t* range_table;     // bf16 kernel: first tile of each tail range (n_ranges + 1), written by the attention kernel
   float* lse;               // optional [heads, n_q]: log of the softmax denominator (natural log)

@@ -14,7 +14,8 @@ hipError_t launch_pool(const PoolArgs& a, int n_blocks, bool bf16, hipStream_t s
 // blocks followed by the combine of split items; fp32: a.n_blocks items, each
 // over a.key_splits blocks, followed by their combine.
 hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t stream);
-hipError_t launch_forward_f32(const FwdArgs& a, int head_dim, hipStream_t stream);  // its fp32 half
+hipError_t launch_forward_f32(const FwdArgs& a, int head_dim, hipStream_t stream);    // fp32 plans
+hipError_t launch_forward_small(const FwdArgs& a, int head_dim, hipStream_t stream);  // bf16, key_splits > 0
 
 // Backward: rowsum(d_out * out) per head and query.
 hipError_t launch_bwd_dot(const DotArgs& a, bool bf16, hipStream_t stream);

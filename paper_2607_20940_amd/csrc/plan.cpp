@@ -21,6 +21,44 @@ bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
 
 int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / b; }
 
+// Blocks per 32-query item of fwd_small_kernel, or 0 for the persistent
+// 256-query kernel: the one expected to be faster, in nanoseconds fitted on an
+// MI355X over layers of 1 to 18 heads of 64 and 128 and 1e9 to 2e11 FLOP.
+// Small kernel: 6 us and, per step of eight 32-key tiles (one per wave), 1.25
+// us for the longest context, or 1.9 us for the average block where all CUs
+// stream K/V at once; merging S blocks per item adds 5 us and 1.5 us per
+// block.  Persistent kernel: 28 us (its pieces' fill, records and merge) and
+// 1e15 FLOP/s.  Measured, small / persistent: 2 heads of 128 on 10 x 13 18 /
+// 35 us, 6 heads of 64 on 17 x 23 28 / 39 us, 5 heads of 128 on 13 x 18 52 /
+// 51 us, 4 heads of 128 on 15 x 26 with 12 history frames 113 / 80 us.
+int32_t small_layer_splits(const Plan& p, const std::vector<std::vector<int64_t>>& run_tok, int64_t cus) {
+  int64_t longest = 0;
+  double items = 0, steps = 0, flops = 0;
+  for (size_t g = 0; g < p.groups.size(); ++g) {
+    int64_t tiles = 0;
+    for (int64_t n : run_tok[g]) tiles += (n + 31) / 32;
+    const double nq = p.groups[g].q_end - p.groups[g].q_begin;
+    const double it = std::ceil(nq / kFwdF32BM) * p.desc.num_heads;
+    const int64_t st = (tiles + kSplitWaves - 1) / kSplitWaves;
+    longest = std::max(longest, st);
+    items += it;
+    steps += it * st;
+    flops += 4.0 * p.desc.head_dim * p.desc.num_heads * nq * p.groups[g].n_kv;
+  }
+  double best = 28e3 + flops * 1e-6;
+  int32_t splits = 0;
+  for (int32_t s = 1; s <= 8 && s <= longest; s *= 2) {
+    if (s > 1 && items * s > cus) break;
+    const double t = 6e3 + (s > 1 ? 5e3 + 1.5e3 * s : 0.0) +
+                     std::max(1.25e3 * static_cast<double>((longest + s - 1) / s), 1.9e3 * steps / cus);
+    if (t < best) {
+      best = t;
+      splits = s;
+    }
+  }
+  return splits;
+}
+
 }  // namespace
 
 mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks, Plan& p, std::string& err) {
@@ -248,42 +286,54 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
   p.n_ranges = 1;
   const int64_t total = make_schedule(p, run_tok).total_tiles;
   if (slots <= 0) slots = 512;
-  int64_t ranges = attention_blocks > 0 ? attention_blocks : std::min<int64_t>(slots, n_items);
-  ranges = std::max<int64_t>(1, std::min<int64_t>(ranges, total));
-  p.n_ranges = static_cast<int32_t>(ranges);
-  p.sched = make_schedule(p, run_tok);
-  p.partial_off = 0;
-  p.partial_bytes = 0;
+  // Workspace after the pooled blocks.  Where there is a choice of schedule,
+  // one whose records would push a plan past the scratch of the entry point
+  // without allocations is passed over if another one fits.
+  const int64_t room = MSSA_NOALLOC_SCRATCH_BYTES - ws;
+  auto range_bytes = [&](int64_t n) {  // partial records and range table of n tile ranges
+    return n > 1 ? align256(2 * n * partial_record_floats(d.head_dim) * 4) + align256((n + 1) * 8) : 0;
+  };
+  int64_t items32 = 0;
+  for (const QGroup& g : p.groups)
+    items32 += static_cast<int64_t>((g.q_end - g.q_begin + kFwdF32BM - 1) / kFwdF32BM) * d.num_heads;
+  auto split_bytes = [&](int64_t s) {
+    return s > 1 ? align256(items32 * s * split_record_floats(d.head_dim) * 4) : 0;
+  };
+  p.partial_off = ws;
   p.range_table_off = 0;
-  if (d.dtype == MSSA_BF16 && p.n_ranges > 1) {
-    const int64_t rec_bytes = align256(2 * static_cast<int64_t>(p.n_ranges) * partial_record_floats(d.head_dim) * 4);
-    p.partial_off = ws;
-    p.range_table_off = ws + rec_bytes;
-    p.partial_bytes = rec_bytes + align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
-    ws += p.partial_bytes;
-  }
   if (d.dtype == MSSA_F32) {
     // The eight waves of a block take 32-key tiles in turn; a context is
     // split over several blocks while that leaves every wave a tile and the
     // items alone leave CUs idle.
-    int64_t items = 0, tiles = 0;
+    int64_t tiles = 0;
     for (int g = 0; g < G; ++g) {
-      items += static_cast<int64_t>((p.groups[g].q_end - p.groups[g].q_begin + kFwdF32BM - 1) / kFwdF32BM) * d.num_heads;
       int64_t t = 0;
       for (const Run& r : p.runs[g]) t += (r.n_tok + 31) / 32;
       tiles = std::max(tiles, t);
     }
-    const int64_t s = std::max<int64_t>(1, std::min(slots / items, (tiles + kSplitWaves - 1) / kSplitWaves));
-    const int64_t bytes = align256(items * s * split_record_floats(d.head_dim) * 4);
-    // never so large that the entry point without allocations, which took
-    // the plan without records, would refuse it
-    if (s > 1 && (ws + bytes <= MSSA_NOALLOC_SCRATCH_BYTES || ws > MSSA_NOALLOC_SCRATCH_BYTES)) {
-      p.key_splits = static_cast<int32_t>(s);
-      p.partial_off = ws;
-      p.partial_bytes = bytes;
-      ws += bytes;
+    int64_t s = std::max<int64_t>(1, std::min(slots / items32, (tiles + kSplitWaves - 1) / kSplitWaves));
+    if (room >= 0 && split_bytes(s) > room) s = 1;
+    p.key_splits = static_cast<int32_t>(s);
+    p.partial_bytes = split_bytes(s);
+  } else {
+    int64_t ranges = attention_blocks;
+    if (attention_blocks <= 0) {
+      p.key_splits = small_layer_splits(p, run_tok, slots);
+      if (room >= 0 && split_bytes(p.key_splits) > room) p.key_splits = 1;
+      // One range per resident block, of two tiles at least: a layer of few
+      // items is split rather than left on few CUs.  Pass of 4 heads of 128
+      // on 15 x 26 (56 items): 167 us at one range per item, 80 at 256
+      // ranges; with under two tiles a range its record costs more than it
+      // saves (2 heads on 10 x 13, 250 tiles: 36 us at 160, 42 at 256).
+      ranges = p.key_splits > 0 ? 1 : std::min<int64_t>(slots, std::max<int64_t>(n_items, total / 2));
+      if (room >= 0 && range_bytes(std::min(ranges, total)) > room) ranges = std::min<int64_t>(slots, n_items);
     }
+    p.n_ranges = static_cast<int32_t>(std::max<int64_t>(1, std::min(ranges, total)));
+    p.partial_bytes = p.key_splits > 0 ? split_bytes(p.key_splits) : range_bytes(p.n_ranges);
+    if (p.n_ranges > 1) p.range_table_off = ws + p.partial_bytes - align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
   }
+  p.sched = make_schedule(p, run_tok);
+  ws += p.partial_bytes;
   p.workspace_bytes = ws;
 
   // Backward workspace and the scatter of context gradients to the sources.

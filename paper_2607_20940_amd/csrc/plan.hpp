@@ -115,7 +115,9 @@ struct Plan {
   Schedule sched;
   int64_t partial_off, partial_bytes;    // partial records and the range table in the workspace
   int64_t range_table_off;               // n_ranges + 1 int64 first tiles of the tail ranges
-  int32_t key_splits = 1;                // fp32 plans: blocks that share the context of one 32-query item
+  // Blocks that share the context of one 32-query item: fp32 plans (>= 1) and
+  // bf16 plans of small layers; 0: the persistent 256-query kernel.
+  int32_t key_splits = 0;
   // Backward workspace: the forward's, then -rowsum(dO * O) [heads, n_q]
   // fp32, -lse / scale [heads, n_q] fp32, then per group the fp32 context
   // gradients of K and V, then (bf16) per group the dS tiles.

@@ -1,0 +1,40 @@
+"""Workspace of plans that choose between schedules (no GPU needed): the
+records a schedule needs never push a plan past the scratch of the entry point
+without allocations when another schedule fits."""
+
+import pytest
+
+from paper_2607_20940_amd import mssa
+
+SCRATCH = mssa.MSSA_NOALLOC_SCRATCH_BYTES
+
+
+def _plan(hist, dtype, blocks=0, heads=1, grid=64):
+    desc = dict(num_states=2, scales=[1, 2], grid_h=grid, grid_w=grid, frames_per_state=1, sink_frames=0,
+                hist_frames=hist, num_heads=heads, head_dim=128, dtype=dtype)
+    return mssa.mssa_plan_create_ex(desc, blocks)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_long_history_of_one_head_fits_the_scratch(dtype):
+    """One head on a long history: few query items (20 of 256 queries) whose
+    pooled history alone takes most of the scratch."""
+    eb = 2 if dtype == "bf16" else 4
+    for hist in (100, 200, 300, 400, 500):
+        pooled = 2 * (hist + 1) * 32 * 32 * 128 * eb
+        small = 2 * 20 * 256 * (128 + 2) * 4 if dtype == "bf16" else 0  # records of one range per item
+        ws = _plan(hist, dtype).info()["workspace_bytes"]
+        assert ws >= pooled
+        if pooled + small + 4096 <= SCRATCH:
+            assert ws <= SCRATCH, hist
+    # away from the limit the records are there: a range per pair of tiles
+    assert dtype == "f32" or _plan(100, dtype).info()["workspace_bytes"] > 2 * 101 * 32 * 32 * 128 * eb + small
+
+
+def test_given_attention_blocks_are_kept():
+    """A given number of blocks is the number of ranges, whatever the layer."""
+    rec = 2 * 256 * (128 + 2) * 4
+    for blocks in (2, 7, 97):
+        base = _plan(4, "bf16", 1, grid=32).info()["workspace_bytes"]
+        ws = _plan(4, "bf16", blocks, grid=32).info()["workspace_bytes"]
+        assert ws == base + blocks * rec + ((blocks + 1) * 8 + 255) // 256 * 256
