@@ -199,20 +199,21 @@ int64_t frame_tokens(const mssa::Plan& p, int32_t s) {
   return gh * gw;
 }
 
-// Validation and slot assignment shared by both appends; enqueues the native
-// frame copies.  On success *ring_head / *ring_count are advanced and slots
-// holds the ring slot of each appended frame.
-mssa_status append_native(const mssa::Plan& p, const void* k_win, const void* v_win, void* k_ring, void* v_ring,
-                          int32_t ring_cap_frames, int32_t* ring_head, int32_t* ring_count,
-                          std::vector<int32_t>& slots, void* stream) {
+// Validation and slot assignment shared by both appends; nothing is enqueued.
+// On success head / count are those after the append and slots holds the ring
+// slot of each appended frame.
+mssa_status append_check(const mssa::Plan& p, const void* k_win, const void* v_win, void* k_ring, void* v_ring,
+                         int32_t ring_cap_frames, const int32_t* ring_head, const int32_t* ring_count, int32_t* head,
+                         int32_t* count, std::vector<int32_t>& slots) {
   if (!k_win || !v_win || !k_ring || !v_ring || !ring_head || !ring_count)
     return fail(MSSA_ERR_INVALID_ARG, "null argument");
   const int32_t F = p.desc.frames_per_state;
   if (p.desc.scales[0] != 1)
     return fail(MSSA_ERR_UNSUPPORTED, "the emitted head state must be at native scale (scales[0] == 1)");
   if (ring_cap_frames < F) return fail(MSSA_ERR_UNSUPPORTED, "ring_cap_frames < frames_per_state");
-  int32_t head = *ring_head, count = *ring_count;
-  if (!ring_slots(ring_cap_frames, F, &head, &count, slots))
+  *head = *ring_head;
+  *count = *ring_count;
+  if (!ring_slots(ring_cap_frames, F, head, count, slots))
     return fail(MSSA_ERR_INVALID_ARG, "inconsistent ring_head / ring_count");
   const size_t frame_bytes = static_cast<size_t>(p.tok1 * p.ld * p.elem_bytes);
   const char* kw = static_cast<const char*>(k_win);
@@ -226,19 +227,70 @@ mssa_status append_native(const mssa::Plan& p, const void* k_win, const void* v_
       overlap(vr, ring_bytes, kw, win_bytes) || overlap(vr, ring_bytes, vw, win_bytes) ||
       overlap(kr, ring_bytes, vr, ring_bytes))
     return fail(MSSA_ERR_INVALID_ARG, "ring buffers overlap each other or the window");
-  const hipStream_t st = static_cast<hipStream_t>(stream);
-  for (int32_t f = 0; f < F; ++f) {
-    const size_t slot = static_cast<size_t>(slots[f]);
-    mssa_status s = check_device(hipMemcpyAsync(kr + slot * frame_bytes, kw + f * frame_bytes, frame_bytes,
-                                                hipMemcpyDeviceToDevice, st), "history append (K)");
-    if (s != MSSA_OK) return s;
-    s = check_device(hipMemcpyAsync(vr + slot * frame_bytes, vw + f * frame_bytes, frame_bytes,
-                                    hipMemcpyDeviceToDevice, st), "history append (V)");
-    if (s != MSSA_OK) return s;
-  }
-  *ring_head = head;
-  *ring_count = count;
   return MSSA_OK;
+}
+
+// One frame's K and V into a ring slot, gh x gw tokens.
+mssa::PoolJobArgs frame_copy(const char* k, const char* v, char* dst_k, char* dst_v, int32_t gh, int32_t gw) {
+  mssa::PoolJobArgs A{};
+  A.src_k = k;
+  A.src_v = v;
+  A.dst_k = dst_k;
+  A.dst_v = dst_v;
+  A.src_gh = A.dst_gh = gh;
+  A.src_gw = A.dst_gw = gw;
+  A.factor = 1;
+  A.n_frames = 1;
+  return A;
+}
+
+// Enqueues frame copies: all in one launch where every address is 16-byte
+// aligned (frames are whole multiples of 128 bytes), device copies otherwise.
+mssa_status launch_copies(const mssa::Plan& p, std::vector<mssa::PoolJobArgs>& jobs, void* stream) {
+  const int64_t row_bytes = p.ld * p.elem_bytes;
+  bool aligned = true;
+  for (const mssa::PoolJobArgs& A : jobs)
+    for (const void* t : {A.src_k, A.src_v, static_cast<const void*>(A.dst_k), static_cast<const void*>(A.dst_v)})
+      aligned = aligned && aligned16(t);
+  if (!aligned) {
+    for (const mssa::PoolJobArgs& A : jobs) {
+      const size_t bytes = static_cast<size_t>(int64_t{A.dst_gh} * A.dst_gw * row_bytes);
+      mssa_status s = check_device(hipMemcpyAsync(A.dst_k, A.src_k, bytes, hipMemcpyDeviceToDevice,
+                                                  static_cast<hipStream_t>(stream)), "history append (K)");
+      if (s != MSSA_OK) return s;
+      s = check_device(hipMemcpyAsync(A.dst_v, A.src_v, bytes, hipMemcpyDeviceToDevice,
+                                      static_cast<hipStream_t>(stream)), "history append (V)");
+      if (s != MSSA_OK) return s;
+    }
+    return MSSA_OK;
+  }
+  // frames that follow one another in source and destination are one job
+  std::vector<mssa::PoolJobArgs> merged;
+  for (const mssa::PoolJobArgs& A : jobs) {
+    if (!merged.empty()) {
+      mssa::PoolJobArgs& B = merged.back();
+      const int64_t bytes = B.n_frames * int64_t{B.dst_gh} * B.dst_gw * row_bytes;
+      if (B.dst_gh == A.dst_gh && B.dst_gw == A.dst_gw && static_cast<const char*>(B.src_k) + bytes == A.src_k &&
+          static_cast<const char*>(B.src_v) + bytes == A.src_v && static_cast<char*>(B.dst_k) + bytes == A.dst_k &&
+          static_cast<char*>(B.dst_v) + bytes == A.dst_v) {
+        ++B.n_frames;
+        continue;
+      }
+    }
+    merged.push_back(A);
+  }
+  return launch_pool_jobs(p, merged, stream);
+}
+
+// The head state's native frames into their slots.
+void native_copies(const mssa::Plan& p, const void* k_win, const void* v_win, void* k_ring, void* v_ring,
+                   const std::vector<int32_t>& slots, std::vector<mssa::PoolJobArgs>& jobs) {
+  const int64_t frame_bytes = p.tok1 * p.ld * p.elem_bytes;
+  for (size_t f = 0; f < slots.size(); ++f)
+    jobs.push_back(frame_copy(static_cast<const char*>(k_win) + static_cast<int64_t>(f) * frame_bytes,
+                              static_cast<const char*>(v_win) + static_cast<int64_t>(f) * frame_bytes,
+                              static_cast<char*>(k_ring) + slots[f] * frame_bytes,
+                              static_cast<char*>(v_ring) + slots[f] * frame_bytes, p.desc.grid_h, p.desc.grid_w));
 }
 
 // mssa_forward / mssa_forward_ring: validate, pack the kernel arguments and
@@ -980,9 +1032,19 @@ mssa_status mssa_hist_append(mssa_plan plan, const void* k_win, const void* v_wi
                              int32_t ring_cap_frames, int32_t* ring_head, int32_t* ring_count, void* stream) {
   return guarded("mssa_hist_append", [&]() -> mssa_status {
     if (!plan) return fail(MSSA_ERR_INVALID_ARG, "null argument");
+    const mssa::Plan& p = plan->p;
     std::vector<int32_t> slots;
-    return append_native(plan->p, k_win, v_win, k_ring, v_ring, ring_cap_frames, ring_head, ring_count, slots,
-                         stream);
+    int32_t head = 0, count = 0;
+    mssa_status s = append_check(p, k_win, v_win, k_ring, v_ring, ring_cap_frames, ring_head, ring_count, &head,
+                                 &count, slots);
+    if (s != MSSA_OK) return s;
+    std::vector<mssa::PoolJobArgs> jobs;
+    native_copies(p, k_win, v_win, k_ring, v_ring, slots, jobs);
+    s = launch_copies(p, jobs, stream);
+    if (s != MSSA_OK) return s;
+    *ring_head = head;
+    *ring_count = count;
+    return MSSA_OK;
   });
 }
 
@@ -1006,37 +1068,36 @@ mssa_status mssa_hist_append_ring(mssa_plan plan, const void* k_win, const void*
     if (coarse && (!workspace || workspace_bytes < p.workspace_bytes))
       return fail(MSSA_ERR_WORKSPACE, "workspace smaller than mssa_plan_info.workspace_bytes");
     std::vector<int32_t> slots;
-    const mssa_status s0 = append_native(p, k_win, v_win, k_ring, v_ring, ring_cap_frames, ring_head, ring_count,
-                                         slots, stream);
-    if (s0 != MSSA_OK) return s0;
+    int32_t head = 0, count = 0;
+    mssa_status s = append_check(p, k_win, v_win, k_ring, v_ring, ring_cap_frames, ring_head, ring_count, &head,
+                                 &count, slots);
+    if (s != MSSA_OK) return s;
+    std::vector<mssa::PoolJobArgs> jobs;
+    native_copies(p, k_win, v_win, k_ring, v_ring, slots, jobs);
     // The head state's frames pooled to each coarse scale: window frames
     // 0 .. F-1 of that group's context, which mssa_pool_kv wrote to the
     // group's pooled block.
     const int64_t row_bytes = p.ld * p.elem_bytes;
     const char* ws = static_cast<const char*>(workspace);
-    const hipStream_t st = static_cast<hipStream_t>(stream);
     for (size_t g = 0; g < p.groups.size(); ++g) {
       const int32_t sc = p.groups[g].scale;
       if (sc == 1) continue;
-      const int64_t tok_s = frame_tokens(p, sc);
-      const size_t fbytes = static_cast<size_t>(tok_s * row_bytes);
+      const int32_t gh = (p.desc.grid_h + sc - 1) / sc, gw = (p.desc.grid_w + sc - 1) / sc;
       for (const mssa::SegRow& r : p.segs) {
         if (r.q_scale != sc || r.kind != mssa::kWin || r.frame >= p.desc.frames_per_state) continue;
-        if (r.buffer != mssa::kBufPooled || r.n_tok != tok_s)
+        if (r.buffer != mssa::kBufPooled || r.n_tok != int64_t{gh} * gw)
           return fail(MSSA_ERR_UNSUPPORTED, "head frames are not pooled to a coarse scale in this plan");
-        const size_t slot = static_cast<size_t>(slots[r.frame]);
-        mssa_status s = check_device(
-            hipMemcpyAsync(static_cast<char*>(k_ring_pooled[g]) + slot * fbytes,
-                           ws + p.pooled_k_off[g] + r.tok_offset * row_bytes, fbytes, hipMemcpyDeviceToDevice, st),
-            "pooled history append (K)");
-        if (s != MSSA_OK) return s;
-        s = check_device(
-            hipMemcpyAsync(static_cast<char*>(v_ring_pooled[g]) + slot * fbytes,
-                           ws + p.pooled_v_off[g] + r.tok_offset * row_bytes, fbytes, hipMemcpyDeviceToDevice, st),
-            "pooled history append (V)");
-        if (s != MSSA_OK) return s;
+        const int64_t dst = slots[r.frame] * int64_t{r.n_tok} * row_bytes;
+        jobs.push_back(frame_copy(ws + p.pooled_k_off[g] + r.tok_offset * row_bytes,
+                                  ws + p.pooled_v_off[g] + r.tok_offset * row_bytes,
+                                  static_cast<char*>(k_ring_pooled[g]) + dst,
+                                  static_cast<char*>(v_ring_pooled[g]) + dst, gh, gw));
       }
     }
+    s = launch_copies(p, jobs, stream);
+    if (s != MSSA_OK) return s;
+    *ring_head = head;
+    *ring_count = count;
     return MSSA_OK;
   });
 }

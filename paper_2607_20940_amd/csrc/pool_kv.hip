@@ -6,6 +6,10 @@
 // copies the block's first cell instead: the same loop over a 1 x 1 block,
 // whose sum divided by 1 is the source value exactly.
 //
+// Jobs of factor 1 copy frames: the cache roll of all a layer's rings in one
+// launch (12 device copies of 2-5 us each before: 4 heads on 15 x 26, 40 us of
+// a 104 us layer pass).
+//
 // HBM-bound: every source byte is read once and every pooled byte written
 // once (frames pooled both by 2 and by 4 are read once for both).  One thread
 // produces one 16-byte chunk of one pooled token (of the coarser level when
@@ -165,7 +169,11 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(PoolArgs a) {
   const int64_t idx = static_cast<int64_t>(b - J.block_begin) * kPoolThreads + threadIdx.x;
   if (idx >= total) return;
   const bool is_v = blockIdx.y != 0;
-  if (J.levels == 2) {
+  if (J.factor == 1) {
+    // a plain copy of whole frames (the cache roll), bit for bit
+    const auto* s = static_cast<const uint4*>(is_v ? J.src_v : J.src_k);
+    static_cast<uint4*>(is_v ? J.dst_v : J.dst_k)[idx] = s[idx];
+  } else if (J.levels == 2) {
     pool_cell<T, 4, true>(a, J, idx, is_v);  // factors 2 and 4 (the only fused pair)
   } else if (!a.pick_first && J.factor == 2) {
     pool_cell<T, 2, false>(a, J, idx, is_v);
