@@ -557,6 +557,8 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
         }
     }
   } else {
+    // channels 4 c .. 4 c + 3 of query n of the wave at (c * 32 + n) * 4: each
+    // store of the wave is 1 KB in one piece
     float* ro = a.partial + static_cast<int64_t>(rec) * partial_record_floats(D);
     const int ql = wave * 32 + n;
 #pragma unroll
@@ -566,7 +568,7 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = o[db][4 * jj + i];
-        *reinterpret_cast<f32x4*>(ro + ql * D + db * 32 + 8 * jj + 4 * hh) = v;
+        *reinterpret_cast<f32x4*>(ro + wave * 32 * D + ((8 * db + 2 * jj + hh) * 32 + n) * 4) = v;
       }
     if (hh == 0) {
       ro[BM * D + ql] = m_run;
@@ -624,14 +626,17 @@ void fwd_bf16_kernel(FwdArgs a) {
 
 // Merge the pieces of items split across ranges.  Block (j, y) looks at tail
 // range j: if the range ends inside an item whose first tile it holds, it
-// combines queries [y QS, (y + 1) QS) of all of that item's pieces (ranges
+// combines queries [32 y, 32 y + 32) of all of that item's pieces (ranges
 // j .. j1) in range order.  Range bounds come from the table the attention
-// kernel wrote.  Each thread owns one float4 of the output and loads it from
-// up to kMaxMerge pieces at once (an item of the tail may be cut into many
-// short pieces), then merges them in order.
+// kernel wrote.  Latency-bound: most blocks only find that they have nothing
+// to do, and the others walk a short chain of dependent loads, so a block
+// takes a whole 32-query slice (D / 32 float4 of the output per thread, their
+// loads and those of kMaxMerge pieces in flight together): with one float4
+// per thread and four times the blocks 12.8 us where every CU has a range (4
+// heads of 128 on 15 x 26).
 template <int D>
 __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
-  constexpr int BM = kFwdBM, QS = kCombineThreads * 4 / D, kMaxMerge = 8;
+  constexpr int BM = kFwdBM, kMaxMerge = 4, NV = 32 * D / 4 / kCombineThreads;
   const int64_t* tab = a.range_table;
   const int j = blockIdx.x;
   const int64_t S = tab[j], E = tab[j + 1];
@@ -641,6 +646,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
   const int64_t T = L.item_begin;
   if (S > T) return;                         // the item's first piece is in an earlier range
   const FwdGroupArgs& G = a.groups[L.g];
+  const int head = L.item / G.n_qtiles;
+  const int qtile = L.item - head * G.n_qtiles;
+  const int y = blockIdx.y;
+  const int q0 = G.q_begin + qtile * BM + y * 32;
+  if (q0 >= G.q_end) return;
   const int64_t Tend = T + G.tiles_per_item;
   // Last range holding a piece of the item: the table is nondecreasing.
   int j1 = j;
@@ -650,16 +660,16 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
     j1 += cnt;
     if (cnt < kCombineThreads) break;
   }
-  const int head = L.item / G.n_qtiles;
-  const int qtile = L.item - head * G.n_qtiles;
   const int64_t rec_len = partial_record_floats(D);
-  const int ql = blockIdx.y * QS + static_cast<int>(threadIdx.x) / (D / 4), d4 = threadIdx.x % (D / 4);
+  const int tid = threadIdx.x, q = tid & 31;  // kCombineThreads is a multiple of 32: every float4 of a thread is query q's
   // Pieces are merged in range order with a running max, like the online
   // softmax itself.
-  f32x4 acc = f32x4{};
+  f32x4 acc[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) acc[v] = f32x4{};
   float m = -INFINITY, l = 0.f;
   for (int base = j; base <= j1; base += kMaxMerge) {
-    f32x4 ov[kMaxMerge];
+    f32x4 ov[kMaxMerge][NV];
     float mv[kMaxMerge], lv[kMaxMerge];
     bool have[kMaxMerge];
 #pragma unroll
@@ -668,9 +678,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
       have[i] = jj <= j1 && tab[jj] < tab[jj + 1];  // ranges inside the span may be empty
       if (have[i]) {
         const float* ro = a.partial + (jj > j || S == T ? 2 * jj : 2 * jj + 1) * rec_len;
-        ov[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(ro + ql * D + 4 * d4));
-        mv[i] = ro[BM * D + ql];
-        lv[i] = ro[BM * D + BM + ql];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          ov[i][v] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(ro + y * 32 * D) + v * kCombineThreads + tid);
+        mv[i] = ro[BM * D + y * 32 + q];
+        lv[i] = ro[BM * D + BM + y * 32 + q];
       }
     }
 #pragma unroll
@@ -678,20 +690,23 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
       if (!have[i]) continue;
       const float mn = fmaxf(m, mv[i]);
       const float so = __builtin_amdgcn_exp2f(m - mn), sj = __builtin_amdgcn_exp2f(mv[i] - mn);
-      acc = acc * so + sj * ov[i];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) acc[v] = acc[v] * so + sj * ov[i][v];
       l = l * so + sj * lv[i];
       m = mn;
     }
   }
-  const int q_row = G.q_begin + qtile * BM + ql;
-  if (q_row >= G.q_end) return;
+  if (q0 + q >= G.q_end) return;
   const float inv = 1.0f / l;
-  if (a.lse && d4 == 0) a.lse[static_cast<int64_t>(head) * a.n_q + q_row] = (m + log2f(l)) * kLn2;
-  bf16x4 v;
+  if (a.lse && tid < 32) a.lse[static_cast<int64_t>(head) * a.n_q + q0 + q] = (m + log2f(l)) * kLn2;
+  __bf16* op = static_cast<__bf16*>(a.out) + static_cast<int64_t>(q0 + q) * a.ld + static_cast<int64_t>(head) * D;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = static_cast<__bf16>(acc[i] * inv);
-  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(a.out) + static_cast<int64_t>(q_row) * a.ld +
-                             static_cast<int64_t>(head) * D + 4 * d4) = v;
+  for (int v = 0; v < NV; ++v) {
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = static_cast<__bf16>(acc[v][i] * inv);
+    *reinterpret_cast<bf16x4*>(op + ((v * kCombineThreads + tid) >> 5) * 4) = o;
+  }
 }
 
 }  // namespace
@@ -711,9 +726,9 @@ hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_ranges < 2) return e;
     if (head_dim == 128)
-      hipLaunchKernelGGL(combine_kernel<128>, dim3(a.n_ranges - 1, kFwdBM * 128 / 4 / kCombineThreads), dim3(kCombineThreads), 0, stream, a);
+      hipLaunchKernelGGL(combine_kernel<128>, dim3(a.n_ranges - 1, kFwdBM / 32), dim3(kCombineThreads), 0, stream, a);
     else
-      hipLaunchKernelGGL(combine_kernel<64>, dim3(a.n_ranges - 1, kFwdBM * 64 / 4 / kCombineThreads), dim3(kCombineThreads), 0, stream, a);
+      hipLaunchKernelGGL(combine_kernel<64>, dim3(a.n_ranges - 1, kFwdBM / 32), dim3(kCombineThreads), 0, stream, a);
     return hipGetLastError();
   }
   return launch_forward_f32(a, head_dim, stream);

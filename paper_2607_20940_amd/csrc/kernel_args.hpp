@@ -15,7 +15,7 @@ constexpr int kMaxPoolJobs = 16;   // pool jobs per launch
 constexpr int kFwdBM = 256;
 constexpr int kFwdBN = 64;
 constexpr int kFwdThreads = 512;
-// Merge of split items: threads per block (one output float4 each).
+// Merge of split items: threads per block (32 queries of an item).
 constexpr int kCombineThreads = 256;
 // Kernels whose eight waves split the context of 32 queries (fp32 plans, and
 // the bf16 forward of small layers): queries per item, waves per block.
@@ -64,8 +64,9 @@ struct FwdArgs {
   FwdGroupArgs groups[kMaxGroups];  // in launch order (longest context first)
 };
 
-// One partial record: unnormalised O [BM][D] (fp32), running max m [BM] and
-// row sum l [BM] of one piece of an item that spans several tile ranges.
+// One partial record: unnormalised O of 256 queries (fp32, [wave][D / 4][32
+// queries][4 channels]), running max m [BM] and row sum l [BM] of one piece of
+// an item that spans several tile ranges.
 constexpr int64_t partial_record_floats(int head_dim) { return static_cast<int64_t>(kFwdBM) * (head_dim + 2); }
 
 // One record of an item whose context is split over key_splits blocks: O
