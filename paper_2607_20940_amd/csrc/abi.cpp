@@ -868,6 +868,30 @@ mssa_status tier_layout(const mssa::Plan& p, const mssa_tier_desc* t, std::vecto
   return MSSA_OK;
 }
 
+// The patches of one tier of a latent [frames, C, H, W].
+mssa::PatchArgs tier_patch(const TierGroup& t, const mssa_tier_desc* tier, void* latent, void* rows, int32_t H,
+                           int32_t W) {
+  mssa::PatchArgs pa{};
+  pa.latent = latent;
+  pa.rows = rows;
+  pa.frame0 = t.frame0;
+  pa.n_frames = t.n_frames;
+  pa.C = tier->latent_channels;
+  pa.H = H;
+  pa.W = W;
+  pa.P = t.P;
+  pa.gh = (H + t.P - 1) / t.P;
+  pa.gw = (W + t.P - 1) / t.P;
+  return pa;
+}
+
+// The tiers that move their own patches, in one launch.
+mssa_status launch_tiers(std::vector<mssa::GemmArgs>& ga, const char* what, hipStream_t hs) {
+  if (ga.empty()) return MSSA_OK;
+  for (size_t i = 0; i + 1 < ga.size(); ++i) ga[i].next = &ga[i + 1];
+  return check_device(mssa::launch_gemm_split(ga[0], nullptr, hs), what);
+}
+
 }  // namespace
 
 mssa_status mssa_tier_workspace_size(mssa_plan plan, const mssa_tier_desc* tier, int64_t* bytes) {
@@ -896,22 +920,13 @@ mssa_status mssa_patch_embed(mssa_plan plan, const mssa_tier_desc* tier, const v
       if (!w_embed[g] || !b_embed[g] || !aligned16(w_embed[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
+    std::vector<mssa::PatchArgs> patch(tg.size());
+    std::vector<mssa::GemmArgs> fused;
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
-      mssa::PatchArgs pa{};
-      pa.latent = const_cast<void*>(latent);
-      pa.rows = static_cast<char*>(workspace) + t.rows_off;
-      pa.frame0 = t.frame0;
-      pa.n_frames = t.n_frames;
-      pa.C = tier->latent_channels;
-      pa.H = H;
-      pa.W = W;
-      pa.P = t.P;
-      pa.gh = (H + t.P - 1) / t.P;
-      pa.gw = (W + t.P - 1) / t.P;
-      s = check_device(mssa::launch_patchify(pa, hs), "patchify launch");
-      if (s != MSSA_OK) return s;
+      mssa::PatchArgs& pa = patch[g];
+      pa = tier_patch(t, tier, const_cast<void*>(latent), static_cast<char*>(workspace) + t.rows_off, H, W);
       mssa::GemmArgs ga{};
       ga.y0_scale = 1.f;
       ga.x = pa.rows;
@@ -924,11 +939,20 @@ mssa_status mssa_patch_embed(mssa_plan plan, const mssa_tier_desc* tier, const v
       ga.split = hid;
       ga.ldx = t.kp;
       ga.ldy = hid;
+      ga.fuse = mssa::kFuseEmbed;
+      ga.patch = &pa;
+      if (mssa::tier_fused(ga)) {
+        fused.push_back(ga);
+        continue;
+      }
+      ga.fuse = 0;
+      s = check_device(mssa::launch_patchify(pa, hs), "patchify launch");
+      if (s != MSSA_OK) return s;
       s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
                        "patch embedding GEMM launch");
       if (s != MSSA_OK) return s;
     }
-    return MSSA_OK;
+    return launch_tiers(fused, "patch embedding launch", hs);
   });
 }
 
@@ -950,39 +974,39 @@ mssa_status mssa_patch_unembed(mssa_plan plan, const mssa_tier_desc* tier, const
       if (!w_out[g] || !b_out[g] || !aligned16(w_out[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
+    std::vector<mssa::PatchArgs> patch(tg.size());
+    std::vector<mssa::GemmArgs> fused;
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
+      mssa::PatchArgs& pa = patch[g];
+      pa = tier_patch(t, tier, latent, static_cast<char*>(workspace) + t.rows_off, H, W);
       mssa::GemmArgs ga{};
       ga.y0_scale = 1.f;
       ga.x = static_cast<const char*>(tokens) + static_cast<int64_t>(Q.q_begin) * hid * 2;
       ga.w = w_out[g];
       ga.bias = b_out[g];
-      ga.y[0] = static_cast<char*>(workspace) + t.rows_off;
+      ga.y[0] = pa.rows;
       ga.M = Q.q_end - Q.q_begin;
       ga.N = t.kp;
       ga.K = hid;
       ga.split = t.kp;
       ga.ldx = hid;
       ga.ldy = t.kp;
+      ga.fuse = mssa::kFuseUnembed;
+      ga.patch = &pa;
+      if (mssa::tier_fused(ga)) {
+        fused.push_back(ga);
+        continue;
+      }
+      ga.fuse = 0;
       s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
                        "patch de-embedding GEMM launch");
       if (s != MSSA_OK) return s;
-      mssa::PatchArgs pa{};
-      pa.latent = latent;
-      pa.rows = ga.y[0];
-      pa.frame0 = t.frame0;
-      pa.n_frames = t.n_frames;
-      pa.C = tier->latent_channels;
-      pa.H = H;
-      pa.W = W;
-      pa.P = t.P;
-      pa.gh = (H + t.P - 1) / t.P;
-      pa.gw = (W + t.P - 1) / t.P;
       s = check_device(mssa::launch_unpatchify(pa, hs), "unpatchify launch");
       if (s != MSSA_OK) return s;
     }
-    return MSSA_OK;
+    return launch_tiers(fused, "patch de-embedding launch", hs);
   });
 }
 

@@ -514,4 +514,20 @@ int64_t gemm_split_bytes(int32_t M, int32_t N, int32_t K) {
   return s * tiles * kGemmTile * kGemmTile * 4;
 }
 
+// Fused tiers move pixels in pairs (even patch rows on an even frame width) and
+// take K in whole 64-element stages with 16-byte rows.  The embedding holds a
+// block's patch rows in LDS, K <= 256 of them (36 us -> 22 us for the two tiers
+// of the 1.3B window).  The de-embedding takes 64 x 64 tiles: while the output
+// is narrow (N <= 256: 46 us -> 18 us for that window) or has so few tiles that
+// a 128 x 128 tile would leave the chip idle.
+bool tier_fused(const GemmArgs& a) {
+  const PatchArgs& p = *a.patch;
+  const bool pairs = p.P % 2 == 0 && p.W % 2 == 0 && (p.frame0 + p.n_frames) * p.C * p.H * p.W <= 0x7fffffff;
+  auto at = [](const void* q, uintptr_t n) { return (reinterpret_cast<uintptr_t>(q) & (n - 1)) == 0; };
+  if (!pairs || a.K % kGemmStage != 0) return false;
+  if (a.fuse == kFuseEmbed) return a.K <= 256 && a.N % 8 == 0 && at(a.bias, 8) && at(a.y[0], 16);
+  const int64_t tiles = int64_t{(a.M + kUnembedTile - 1) / kUnembedTile} * ((a.N + kUnembedTile - 1) / kUnembedTile);
+  return (a.N <= 256 || tiles <= 512) && at(a.bias, 2);
+}
+
 }  // namespace mssa

@@ -19,8 +19,13 @@
 //                      direct global -> LDS transfers; gemm256_kernel the
 //                      same in 256 x 256 tiles (K a multiple of 64, at least
 //                      256 rows and features);
-//   unpatchify_kernel  patch rows [tokens, C*P*P] -> latent pixels.
+//   unpatchify_kernel  patch rows [tokens, C*P*P] -> latent pixels;
+//   embed_kernel, unembed_kernel  the two ends with the gather or scatter in
+//                      the GEMM, all tiers in one launch (tier_fused).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
@@ -511,6 +516,296 @@ void gemm256_kernel(GemmArgs a) {
   }
 }
 
+// ------------------------------------------------------------------ fused tiers
+
+__device__ inline const TierProblem& tier_of_block(const TierArgs& a, int b, int& rel) {
+  int g = 0;
+  while (g + 1 < a.n && b >= a.g[g + 1].block_begin) ++g;
+  rel = b - a.g[g].block_begin;
+  return a.g[g];
+}
+
+// Feature k of a patch -> (channel, row, column); P = 2, 4, 8 without divisions.
+__device__ inline void feature_of(int k, int P, int& c, int& dy, int& dx) {
+  if (P == 2) {
+    c = k >> 2, dy = (k >> 1) & 1, dx = k & 1;
+  } else if (P == 4) {
+    c = k >> 4, dy = (k >> 2) & 3, dx = k & 3;
+  } else if (P == 8) {
+    c = k >> 6, dy = (k >> 3) & 7, dx = k & 7;
+  } else {
+    c = k / (P * P);
+    const int r = k - c * P * P;
+    dy = r / P, dx = r - dy * P;
+  }
+}
+
+// Patch embedding of all tiers in one launch.  A block gathers 64 patch rows
+// from the latent once (pairs of pixels, the whole K <= 256 into LDS); then its
+// four waves run on their own, without another barrier: each multiplies the 64
+// rows with 64 features at a time, W fragments straight from L2 into registers
+// (a 64-deep stage ahead), and stores its outputs through 8 KB of LDS of its
+// own as whole 128-byte rows.  Bound by the output's stores (39.5 MB for the
+// 1.3B window) and by latency: the same product with W staged in LDS for the
+// block spent its time in barriers and waits (26-31 us for the window's two
+// tiers, whether two or four blocks shared a CU).
+constexpr int kEmbM = 64, kEmbN = 64, kEmbK = 256;  // rows per block, features per wave step, longest K
+
+__global__ __launch_bounds__(kTierThreads, 2) void embed_kernel(TierArgs a) {
+  constexpr int kXs = kEmbM * kG2K * 2;     // bytes of one 64-deep K slice of the rows
+  constexpr int kE = kEmbM * kEmbN * 2;     // bytes of a wave's output tile
+  constexpr int kWaves = kTierThreads / 64;
+  __shared__ __attribute__((aligned(16))) char lds[kEmbK / kG2K * kXs + kWaves * kE];
+  int rel;
+  const TierProblem& T = tier_of_block(a, blockIdx.x, rel);
+  const PatchArgs& pt = T.patch;
+  const int steps = (T.N + kEmbN - 1) / kEmbN, chunks = (steps + T.tiles_per_block - 1) / T.tiles_per_block;
+  const int tm = rel / chunks, tn0 = rel % chunks * T.tiles_per_block;
+  const int tn1 = min(steps, tn0 + T.tiles_per_block);
+  const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = T.K, nst = K / kG2K;
+
+  // Patch rows tid / 8 and tid / 8 + 32, feature chunk tid % 8 of every slice.
+  const __bf16* latent = static_cast<const __bf16*>(pt.latent);
+  int src[2], ymax[2], xmax[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int t = tm * kEmbM + (tid >> 3) + 32 * i;
+    const int X = t % pt.gw, Y = t / pt.gw % pt.gh, f = t / pt.gw / pt.gh;
+    src[i] = ((static_cast<int>(pt.frame0) + f) * pt.C * pt.H + Y * pt.P) * pt.W + X * pt.P;
+    ymax[i] = t < T.M ? pt.H - Y * pt.P : 0;
+    xmax[i] = pt.W - X * pt.P;
+  }
+  for (int st = 0; st < nst; ++st) {
+    i32x4 px[2];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      int c, dy, dx;
+      feature_of(st * kG2K + (tid & 7) * 8 + 2 * p, pt.P, c, dy, dx);
+      const int off = (c * pt.H + dy) * pt.W + dx;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        px[i][p] = dy < ymax[i] && dx < xmax[i] ? *reinterpret_cast<const int*>(latent + src[i] + off) : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<i32x4*>(reinterpret_cast<__bf16*>(lds + st * kXs) + swz128((tid >> 3) + 32 * i, (tid & 7) * 8)) = px[i];
+  }
+
+  __bf16* E = reinterpret_cast<__bf16*>(lds + kEmbK / kG2K * kXs + wave * kE);
+  const __bf16* B = static_cast<const __bf16*>(T.bias);
+  // X rows n32 and n32 + 32: the swizzle depends on n32 only
+  int xr[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) xr[ks] = swz128(n32, ks * 16 + hh * 8);
+  // W rows (features) of this lane; past the matrix edge the last one, whose
+  // outputs are not stored
+  const __bf16* w[2];
+  auto w_at = [&](int tn) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+      w[cb] = static_cast<const __bf16*>(T.w) + static_cast<int64_t>(min(tn * kEmbN + cb * 32 + n32, T.N - 1)) * K + hh * 8;
+  };
+  bf16x8 wf[2][4];
+  bf16x4 bias[2][4];
+  auto load_w = [&](int st) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) wf[cb][ks] = *reinterpret_cast<const bf16x8*>(w[cb] + st * kG2K + ks * 16);
+  };
+  auto load_bias = [&](int tn) {
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        bias[cb][jj] = *reinterpret_cast<const bf16x4*>(B + min(tn * kEmbN + cb * 32 + 8 * jj + 4 * hh, T.N - 4));
+  };
+  if (tn0 + wave < tn1) {
+    w_at(tn0 + wave);
+    load_w(0);
+    load_bias(tn0 + wave);
+  }
+  __syncthreads();
+  for (int tn = tn0 + wave; tn < tn1; tn += kWaves) {
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) acc[0][cb] = acc[1][cb] = f32x16{};
+    for (int st = 0; st < nst; ++st) {
+      const __bf16* Xs = reinterpret_cast<const __bf16*>(lds + st * kXs);
+      bf16x8 wc[2][4];
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) wc[cb][ks] = wf[cb][ks];
+      // the fragments of the next stage, or of the next step's first
+      if (st + 1 < nst) {
+        load_w(st + 1);
+      } else if (tn + kWaves < tn1) {
+        w_at(tn + kWaves);
+        load_w(0);
+      }
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const bf16x8 xb = *reinterpret_cast<const bf16x8*>(Xs + rb * 32 * kG2K + xr[ks]);
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb)
+            acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[cb][ks], xb, acc[rb][cb], 0, 0, 0);
+        }
+    }
+    // outputs plus bias into the wave's tile (128-byte rows, swizzled), then
+    // whole rows out, 8 threads per row
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          bf16x4 v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            v[i] = static_cast<__bf16>(acc[rb][cb][4 * jj + i] + static_cast<float>(bias[cb][jj][i]));
+          *reinterpret_cast<bf16x4*>(E + rb * 32 * kEmbN + swz128(n32, cb * 32 + 8 * jj + 4 * hh)) = v;
+        }
+    if (tn + kWaves < tn1) load_bias(tn + kWaves);
+    const int col = tn * kEmbN + (lane & 7) * 8;
+    __bf16* y = static_cast<__bf16*>(T.y) + static_cast<int64_t>(tm) * kEmbM * T.N + col;
+#pragma unroll
+    for (int p = 0; p < kEmbM / 8; ++p) {
+      const int rt = p * 8 + (lane >> 3);
+      const bf16x8 v = *reinterpret_cast<const bf16x8*>(E + swz128(rt, (lane & 7) * 8));
+      if (tm * kEmbM + rt < T.M && col < T.N) *reinterpret_cast<bf16x8*>(y + static_cast<int64_t>(rt) * T.N) = v;
+    }
+  }
+}
+
+// Patch de-embedding of all tiers in one launch: 64 tokens x 64 features per
+// block, a 32 x 32 quarter per wave, the whole K in 64-deep stages in flight by
+// direct transfers, and the pixels stored from the epilogue.  Bound by reading
+// the tokens once; narrow tiles so that the 1.3B window's two tiers are 367
+// blocks without splitting K (the split product's partial tiles, their sum and
+// the pass that scattered the patch rows were five launches, 46 us; now 18).
+// kHalves = 1: four waves, four stages in flight (80 KB of LDS, two blocks per
+// CU).  kHalves = 2, where the tiles are no more than the CUs and the chain of
+// stages is what takes the time: eight waves, the second four on the odd
+// stages, whose sums meet in LDS at the end.
+template <int kHalves>
+__global__ __launch_bounds__(kHalves * kTierThreads, 2) void unembed_kernel(TierArgs a) {
+  constexpr int BT = kUnembedTile, kTile = BT * kG2K * 2, NS = kHalves == 1 ? 5 : 8;
+  constexpr int NDMA = kTile / 1024 / (kTierThreads / 64);  // per wave, stage and operand
+  __shared__ __attribute__((aligned(16))) char lds[NS][2][kTile];  // [stage][X | W]
+  int rel;
+  const TierProblem& T = tier_of_block(a, blockIdx.x, rel);
+  const PatchArgs& pt = T.patch;
+  const int tiles_n = (T.N + BT - 1) / BT;
+  const int tm = rel / tiles_n, tn = rel % tiles_n;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave8 & 3, half = wave8 >> 2;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int n32 = lane & 31, hh = lane >> 5;
+  const uint32_t rb = static_cast<uint32_t>(T.K) * 2;
+  uint32_t vo[NDMA];
+#pragma unroll
+  for (int i = 0; i < NDMA; ++i) {
+    const int p = (wave * NDMA + i) * 1024 + 16 * lane;
+    const int row = p >> 7, lc = unswz128(row, (p >> 4) & 7);
+    vo[i] = row * rb + lc * 16;
+  }
+  // rows past the matrix edges fall past the range: zeros
+  const uint32_t xbytes = static_cast<uint32_t>(min(BT, T.M - tm * BT) - 1) * rb + kG2K * 2;
+  const uint32_t wbytes = static_cast<uint32_t>(min(BT, T.N - tn * BT) - 1) * rb + kG2K * 2;
+  const __bf16* X = static_cast<const __bf16*>(T.x) + static_cast<int64_t>(tm) * BT * T.K;
+  const __bf16* W = static_cast<const __bf16*>(T.w) + static_cast<int64_t>(tn) * BT * T.K;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(&lds[0][0][0]));
+  auto issue = [&](int st) {
+    const i32x4 rx = rsrc_of(X + st * kG2K, xbytes), rw = rsrc_of(W + st * kG2K, wbytes);
+    const uint32_t base = lds0 + (st % NS) * 2 * kTile + wave * NDMA * 1024;
+#pragma unroll
+    for (int i = 0; i < NDMA; ++i) {
+      dma16(rx, vo[i], __builtin_amdgcn_readfirstlane(base + i * 1024));
+      dma16(rw, vo[i], __builtin_amdgcn_readfirstlane(base + kTile + i * 1024));
+    }
+  };
+  f32x16 acc = f32x16{};
+  const int nst = T.K / kG2K;
+  // This half's stages are half, half + kHalves, ..; kAhead of them are
+  // requested ahead of the one multiplied.  Both halves make the same number
+  // of rounds (the barrier is the block's).
+  constexpr int kAhead = NS / kHalves - 1;
+  for (int i = 0; i < kAhead; ++i)
+    if (half + i * kHalves < nst) issue(half + i * kHalves);
+  const int rounds = (nst + kHalves - 1) / kHalves;
+  for (int i = 0; i < rounds; ++i) {
+    const int st = half + i * kHalves;
+    // the stage has arrived once only this half's later ones are outstanding
+    const int later = st < nst ? (nst - 1 - st) / kHalves : 0;
+    static_assert(kAhead == 3 || kAhead == 4, "three at most are waited out by count");
+    switch (min(kAhead - 1, later)) {
+      case 3: wait_vmcnt<3 * 2 * NDMA>(); break;
+      case 2: wait_vmcnt<2 * 2 * NDMA>(); break;
+      case 1: wait_vmcnt<2 * NDMA>(); break;
+      default: wait_vmcnt<0>(); break;
+    }
+    __syncthreads();
+    // into the buffer of this half's previous stage, read before this barrier
+    if (st + kAhead * kHalves < nst) issue(st + kAhead * kHalves);
+    if (st < nst) {
+      const __bf16* Xs = reinterpret_cast<const __bf16*>(lds[st % NS][0]);
+      const __bf16* Ws = reinterpret_cast<const __bf16*>(lds[st % NS][1]);
+#pragma unroll
+      for (int ks = 0; ks < kG2K / 16; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            *reinterpret_cast<const bf16x8*>(Ws + swz128(wn * 32 + n32, ks * 16 + hh * 8)),
+            *reinterpret_cast<const bf16x8*>(Xs + swz128(wm * 32 + n32, ks * 16 + hh * 8)), acc, 0, 0, 0);
+    }
+  }
+  __syncthreads();
+  if constexpr (kHalves == 2) {
+    f32x4* P = reinterpret_cast<f32x4*>(&lds[4][0][0]) + wave * 256 + lane;  // past the output tile
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj)
+      if (half) P[jj * 64] = f32x4{acc[4 * jj], acc[4 * jj + 1], acc[4 * jj + 2], acc[4 * jj + 3]};
+    __syncthreads();
+    if (!half) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const f32x4 v = P[jj * 64];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[4 * jj + i] += v[i];
+      }
+    }
+  }
+  // outputs plus bias, rounded to bf16, as [token][feature] (rows of 33 words:
+  // a pair of features read by 64 consecutive tokens hits distinct banks)
+  constexpr int kEStr = BT + 2;
+  __bf16* E = reinterpret_cast<__bf16*>(&lds[0][0][0]);
+  const __bf16* B = static_cast<const __bf16*>(T.bias);
+#pragma unroll
+  for (int e = 0; e < 16 && half == 0; ++e) {
+    const int ct = wn * 32 + 8 * (e >> 2) + 4 * hh + (e & 3), col = tn * BT + ct;
+    const float bv = col < T.N ? static_cast<float>(B[col]) : 0.f;
+    E[(wm * 32 + n32) * kEStr + ct] = static_cast<__bf16>(acc[e] + bv);
+  }
+  __syncthreads();
+  const int t = tm * BT + lane;
+  if (t >= T.M) return;
+  const int X0 = t % pt.gw * pt.P, Y0 = t / pt.gw % pt.gh * pt.P, f = t / pt.gw / pt.gh;
+  __bf16* dst = static_cast<__bf16*>(pt.latent) + (pt.frame0 + f) * pt.C * pt.H * static_cast<int64_t>(pt.W);
+#pragma unroll
+  for (int p = 0; p < BT / 2; p += kHalves * kTierThreads / 64) {
+    const int ct = 2 * (p + wave8), col = tn * BT + ct;
+    int c, dy, dx;
+    feature_of(col, pt.P, c, dy, dx);
+    if (col < T.N && Y0 + dy < pt.H && X0 + dx < pt.W)
+      *reinterpret_cast<uint32_t*>(dst + (c * pt.H + Y0 + dy) * pt.W + X0 + dx) =
+          *reinterpret_cast<const uint32_t*>(E + lane * kEStr + ct);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_patchify(const PatchArgs& a, hipStream_t stream) {
@@ -564,7 +859,58 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+namespace {
+
+hipError_t launch_fused(const GemmArgs& a, hipStream_t stream) {
+  TierArgs t{};
+  const bool embed = a.fuse == kFuseEmbed;
+  const int bm = embed ? kEmbM : kUnembedTile, bn = embed ? kEmbN : kUnembedTile;
+  // Embedding: feature steps per block (a multiple of its four waves) so that
+  // at most about 512 blocks, two per CU and so one round, share the work; a
+  // step costs its K stages and its stores (about 1.5 stages).
+  double work = 0;
+  for (const GemmArgs* p = &a; p; p = p->next)
+    work += std::ceil(p->M / double{kEmbM}) * std::ceil(p->N / double{kEmbN}) * (p->K / kG2K + 1.5);
+  int64_t blocks = 0;
+  for (const GemmArgs* p = &a; p; p = p->next) {
+    if (t.n == kMaxGroups || p->fuse != a.fuse || !tier_fused(*p)) return hipErrorInvalidValue;
+    if (p->M <= 0) continue;
+    TierProblem& g = t.g[t.n++];
+    g.x = p->x;
+    g.w = p->w;
+    g.bias = p->bias;
+    g.y = p->y[0];
+    g.patch = *p->patch;
+    g.M = p->M;
+    g.N = p->N;
+    g.K = p->K;
+    g.block_begin = static_cast<int32_t>(blocks);
+    int64_t tiles_n = (p->N + bn - 1) / bn;
+    if (embed) {
+      const int64_t quads = (tiles_n + 3) / 4;
+      const int64_t most = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(work / 512 / (p->K / kG2K + 1.5) / 4)));
+      const int64_t chunks = (quads + most - 1) / most;
+      g.tiles_per_block = static_cast<int32_t>(4 * ((quads + chunks - 1) / chunks));
+      tiles_n = (tiles_n + g.tiles_per_block - 1) / g.tiles_per_block;
+    }
+    blocks += static_cast<int64_t>((p->M + bm - 1) / bm) * tiles_n;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  }
+  if (blocks == 0) return hipSuccess;
+  const dim3 grid(static_cast<uint32_t>(blocks));
+  if (a.fuse == kFuseEmbed)
+    hipLaunchKernelGGL(embed_kernel, grid, dim3(kTierThreads), 0, stream, t);
+  else if (blocks <= 256)
+    hipLaunchKernelGGL(unembed_kernel<2>, grid, dim3(2 * kTierThreads), 0, stream, t);
+  else
+    hipLaunchKernelGGL(unembed_kernel<1>, grid, dim3(kTierThreads), 0, stream, t);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_gemm_split(const GemmArgs& a, float* partial, hipStream_t stream) {
+  if (a.fuse) return launch_fused(a, stream);
   const int s = gemm_k_splits(a.M, a.N, a.K);
   if (s <= 1 || !partial || !dma_epilogue_ok(a)) return launch_gemm(a, stream);
   GemmArgs b = a;
