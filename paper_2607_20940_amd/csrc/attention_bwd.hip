@@ -17,17 +17,11 @@
 // bf16 path (gfx950 matrix cores, v_mfma_f32_32x32x16_bf16, fp32
 // accumulation), five products in two kernels so that no gradient needs
 // atomics:
-//   dkdv_kernel  pairs of waves sharing a SIMD (two waves per SIMD, 8 per
-//                block); a pair owns 32 context keys and walks the scale's
-//                queries in 64-query stages: wave A S = Q K^T, P (lane =
-//                key) and dV^T += dO^T P; wave B, one stage later, dP = dO
-//                V^T, dS = P (dP - rowsum), dK^T += Q^T dS, with dO^T, Q^T
+//   dkdv_kernel  64 context keys per wave, one wave per SIMD; queries stream in
+//                32-query stages: S = Q K^T, P (lane = key), dV^T += dO^T P, dP =
+//                dO V^T, dS = P (dP - rowsum), dK^T += Q^T dS, with dO^T, Q^T
 //                from transposing reads, and dS (bf16, the value its own
-//                product uses) to a tile in HBM.  Strict ping-pong: in each
-//                of a stage's two barrier-separated phases one wave of the
-//                pair issues only MFMAs and the other only VALU work.  Each
-//                wave holds one operand fragment and one accumulator, which
-//                is what lets two waves share a SIMD.
+//                product uses) to a tile in HBM.
 //   dq_kernel    dQ^T += K^T dS^T over the context, 32 queries per wave, K
 //                rows and the wave's dS tiles streamed through LDS and read
 //                transposed; it reads each dS element once from HBM instead
@@ -40,6 +34,9 @@
 // fp32 plans take the dQ, dK and dV kernels of attention_f32.hip; the rowsum
 // and scatter kernels here serve both.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <utility>
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
@@ -54,7 +51,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 // Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous eighth of the logical blocks so that its L2 serves few heads.
+// contiguous eighth of a group's n blocks so that its L2 serves few heads.  Per
+// group, not over the whole grid: the groups' blocks differ in length (293 and
+// 110 steps of the dK/dV kernel on the 1.3B layer), and contiguous eighths of
+// the grid left the XCDs with the short group idle for 30 % of the kernel.
 __device__ inline int xcd_remap(int b, int n) {
   const int q = n / 8, r = n % 8, x = b % 8, j = b / 8;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
@@ -157,13 +157,11 @@ void dq_kernel(BwdArgs a) {
   static_assert(NK * 1024 * NW == KT && NW * 32 == kBwdQ && BN % 32 == 0 && NDS % 2 == 0, "stage shape");
   __shared__ __attribute__((aligned(16))) char lds[3 * STB];
 
-  int n_blocks = 0;
-  for (int g = 0; g < a.n_groups; ++g) n_blocks += a.groups[g].n_qblocks * a.num_heads;
-  const int b = xcd_remap(blockIdx.x, n_blocks);
+  const int b = blockIdx.x;
   int g = 0;
   while (g + 1 < a.n_groups && b >= a.groups[g + 1].dq_block_begin) ++g;
   const BwdGroupArgs& G = a.groups[g];
-  const int idx = b - G.dq_block_begin;
+  const int idx = xcd_remap(b - G.dq_block_begin, G.n_qblocks * a.num_heads);
   const int hl = idx / G.n_qblocks, qt = idx % G.n_qblocks;  // head of the launch
   const int head = a.head0 + hl;
 
@@ -315,147 +313,169 @@ void dq_kernel(BwdArgs a) {
 
 // ------------------------------------------------------------------ bf16: dK, dV
 
-// dK/dV: a block owns 128 context keys, four pairs of waves of 32 keys each;
-// the waves of a pair share a SIMD.  Wave A (waves 0-3) holds the keys' K
-// fragment and dV accumulator, wave B (waves 4-7) their V fragment and dK
-// accumulator.  Queries stream in 64-query stages t, each taking two phases
-// separated by block barriers, in which one wave of the pair runs MFMAs while
-// the other runs VALU work:
-//   phase 2t:     A  dV^T += dO_{t-1}^T P_{t-1}, then S_t = Q_t K^T
-//                 B  dS_{t-1} = P_{t-1} (dP_{t-1} - rowsum_{t-1})
-//   phase 2t + 1: A  P_t = exp2(S_t c - lse_t), to registers and to LDS for B
-//                 B  dK^T += Q_{t-1}^T dS_{t-1}, then dP_t = dO_t V^T
-// Stage t's Q, dO and row statistics live in LDS buffer t % 4 and are read
-// in phases 2t .. 2t + 3.  A issues stage t + 2 (direct transfers, the
-// statistics included) at the start of its VALU phase 2t + 1 into buffer
-// (t + 2) % 4, whose stage t - 2 was last read in phase 2t - 1, and waits
-// for stage t + 1 at the end of that phase (the transfer instructions cost
-// less there than at the end of the matrix-core phase: -2 %).  B also stores dS_{t-1}
-// to HBM in phase 2t and never waits for memory: a wave's wait for its
-// transfers would also wait for its earlier stores to complete.  P_t is
-// written in phase 2t + 1 and read in 2t + 2; one block per pair suffices.
-// The matrix-core step is one code site for both roles, so that the register
-// allocation holds one set of accumulators, S/dP and P/dS registers.  Its row
-// product starts from an accumulator loaded with the stage's negated row
-// statistics (-lse / scale for A, -rowsum for B), so that S arrives as
-// S - lse / scale (P = exp2(c S'); kQS, queries pre-scaled: c = 1 and
-// P = exp2(S')) and dP as dP - rowsum (dS = P dP').
+// d += a b, with d in ordinary registers (read by VALU instructions later) or
+// in accumulation registers.  Of the 512 registers of a lone wave half are
+// accumulation registers, which VALU instructions cannot read; left to itself
+// the compiler put every product's result there and copied S, dP and their
+// starting values back and forth (264 copies per 64 MFMAs).  It does not see
+// these as matrix instructions, so a VALU read of d has to be two other MFMAs
+// away.
+__device__ inline void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+
+// f(I) for I = 0 .. N - 1 as constants (integral_constant), unrolled by the
+// front end: the unroller gives up on the dK/dV kernel's step.
+template <class F, int... I>
+__device__ __forceinline__ void for_constants(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// d = c + a b, the first product of a chain.
+__device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
+}
+
+// dK/dV: a block owns 256 context keys, four waves (one per SIMD, 512
+// registers) of 64 keys each as two 32-key blocks, so that every operand read
+// from LDS feeds two MFMAs.  Queries stream in 32-query stages t; a step is
+//   A  S_t  = Q_t K^T                (K fragments in registers)
+//   B  dK^T += Q_{t-1}^T dS_{t-1}
+//   C  dP_t = dO_t V^T               (V from the block's 64 KB of LDS)
+//   D  dV^T += dO_t^T P_t
+// of N = D / 16 chunks each: one operand (row read or transposing read, kLead
+// chunks ahead of its use) and its two MFMAs.  What else there is to do is cut
+// into pieces of about four instructions, one behind every MFMA: P_t =
+// exp2(c S_t) during B and C, dS_t = P_t dP_t during D, its stores and the
+// transfers during A.  A wave alone on its SIMD issues one instruction at a
+// time, and an MFMA waits at issue until the one before has left the core (32
+// cycles), so the order within the stream is what keeps the matrix core fed;
+// scheduling barriers hold it.  The loop is unrolled over the stage buffers,
+// which makes every LDS address a lane offset plus an immediate.  Nothing is
+// handed between waves and there is one barrier per step, between C and D.
+// Stage t's Q, dO and row statistics live in LDS buffer t % 4.  Stage t + 2 is
+// requested during A of step t into the buffer of stage t - 2 (last read in B
+// of step t - 1, before that step's barrier); the wait for stage t + 1 comes
+// before the barrier of step t, and D of step t may already read it.  Memory
+// operations complete in order: the wait leaves the younger ones in flight.
+// The row products start from the stage's negated row statistics (-lse / scale,
+// -rowsum), so that S arrives as S - lse / scale (P = exp2(c S'); kQS, queries
+// pre-scaled: c = 1) and dP as dP - rowsum.  dS (bf16, the value the dK product
+// uses) goes to its tile in HBM by range-checked stores at a per-lane offset
+// fixed for the whole kernel.
+// Measured (12 heads of 128, 9360 + 3510 queries on 26910 and 12870 keys): 3.25 -
+// 3.4 ms, matrix cores busy 75 % of the cycles a wave is there, the clock set
+// by power; pairs of waves sharing a SIMD, one on the matrix core and one on
+// the softmax, handing P over through LDS behind two barriers per 64 queries:
+// 4.24 - 4.43 ms, 42 %, 6.8 instructions per MFMA beside it where this has 4.1.
 template <int D, bool kQS>
-__global__ __launch_bounds__(kBwdKVThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(kBwdKVThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void dkdv_kernel(BwdArgs a) {
   using L = Lay<D>;
-  constexpr int KS = L::KS, DB = L::DB;
-  constexpr int BQ = kBwdQS, NQB = BQ / 32;             // queries per stage, 32-query blocks
-  constexpr int QT = BQ * 128 * 2;                      // bytes of one swizzled tile (256-byte rows)
-  constexpr int STB = 2 * QT + 8 * BQ;                  // Q | dO | -lse / scale | -rowsum (fp32)
-  constexpr int NDMA = 2 * QT / 1024 / 4;               // 1 KB transfers per B wave and stage (Q and dO)
-  constexpr int PXB = NQB * 2 * 64 * 16;                // bytes of one pair's P block
-  constexpr int kLead = 4;                              // LDS operands read ahead of their MFMA
-  static_assert(NDMA * 1024 * 4 == 2 * QT && BQ % 32 == 0, "stage shape");
-  constexpr int NBUF = 4;                               // stage buffers
-  __shared__ __attribute__((aligned(16))) char lds[NBUF * STB + 4 * PXB];
+  constexpr int N = L::KS, DB = L::DB;                  // chunks per phase, 32-channel blocks
+  static_assert(N == 2 * DB, "row and transposing phases have the same chunks");
+  constexpr int BQ = kBwdStage;                         // queries per stage
+  constexpr int QT = BQ * 256;                          // bytes of one swizzled tile (256-byte rows)
+  constexpr int STB = 2 * QT;                           // Q | dO
+  constexpr int kStat = 1024;                           // -lse / scale | -rowsum | unused (256 bytes each, 128 used)
+  constexpr int NBUF = 4;
+  constexpr int NDMA = 2 * QT / 1024 / 4;               // 1 KB transfers per wave and stage
+  constexpr int kStat0 = NBUF * STB, kV0 = kStat0 + NBUF * kStat;  // the stages' statistics, the block's V rows
+  constexpr int kLead = 4;                              // chunks an operand is read ahead
+  static_assert(BQ == 32 && NDMA == 4 && kBwdK == 256 && 4 * N % kLead == 0, "stage shape");
+  __shared__ __attribute__((aligned(16))) char lds[kV0 + kBwdK * 256];
 
-  int n_blocks = 0;
-  for (int g = 0; g < a.n_groups; ++g) n_blocks += a.groups[g].n_kblocks * a.num_heads;
-  const int b = xcd_remap(blockIdx.x, n_blocks);
+  const int b = blockIdx.x;
   int g = 0;
   while (g + 1 < a.n_groups && b >= a.groups[g + 1].kv_block_begin) ++g;
   const BwdGroupArgs& G = a.groups[g];
-  const int idx = b - G.kv_block_begin;
+  const int idx = xcd_remap(b - G.kv_block_begin, G.n_kblocks * a.num_heads);
   const int hl = idx / G.n_kblocks, kt = idx % G.n_kblocks;  // head of the launch
   const int head = a.head0 + hl;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pair = wave & 3, role = wave >> 2;  // role 0 (A): S, P, dV; role 1 (B): dP, dS, dK
   const int n = lane & 31, hh = lane >> 5;
-  const int key = kt * kBwdK + pair * 32 + n;
-  const bool k_ok = key < G.n_kv;
   const int64_t ld = a.ld, hoff = static_cast<int64_t>(head) * D;
   const float c = a.scale_log2e;
+  const int key0 = kt * kBwdK + wave * 64 + n;  // this lane's keys: key0, key0 + 32
 
-  // Where B stores its key's dS: byte offset, in the tiles of a 32-query
-  // block, of the key's 64-key stage (its run's stages, as the dQ kernel
-  // walks them), slot and the lane's 8 queries of each tile half (16 hh,
-  // 16 hh + 8 .. of the row's 32 positions); the same offset every stage.
-  // Keys past the context point past the range: the range check drops
-  // their stores, so the store needs no branch.
-  uint32_t ds_voff = kPastEnd;
-  if (role != 0 && k_ok) {
-    int j = key, st = 0, r = 0;
+  // Byte offset, in the tiles of a 32-query block, of the lane's dS of each
+  // key: the key's 64-key stage (its run's stages, as the dQ kernel walks
+  // them), slot and the lane's 8 queries of each tile half.  Keys past the
+  // context point past the range: the range check drops their stores.
+  uint32_t ds_voff[2];
+  bf16x8 kf[2][N];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const int key = key0 + kb * 32;
+    const bool ok = key < G.n_kv;
+    int j = ok ? key : 0, st = 0, r = 0;
     while (r + 1 < G.n_runs && j >= G.runs[r].n_tok) {
       st += (G.runs[r].n_tok + kBwdKS - 1) / kBwdKS;
       j -= G.runs[r].n_tok;
       ++r;
     }
-    ds_voff = static_cast<uint32_t>((st + j / kBwdKS) * (kBwdKS * 64) + (j % kBwdKS) * 32 + 16 * hh);
-  }
-  const uint32_t ds_qbytes = static_cast<uint32_t>(G.ds_stages) * (kBwdKS * 64);  // one 32-query block's tiles
-  const __bf16* const ds_head =
-      static_cast<const __bf16*>(G.ds) + static_cast<int64_t>(hl) * G.ds_qblocks * G.ds_stages * (kBwdKS * 32);
-
-  // B operand of the wave's row product: this lane's key (K for A, V for B),
-  // 8 channels of its half-wave per k step.
-  bf16x8 xf[KS];
-  {
-    const __bf16* xp = ctx_row<__bf16>(G, key, role != 0, ld);
+    ds_voff[kb] = ok ? static_cast<uint32_t>((st + j / kBwdKS) * (kBwdKS * 64) + (j % kBwdKS) * 32 + 16 * hh) : kPastEnd;
+    const __bf16* kp = ctx_row<__bf16>(G, key, false, ld);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      xf[ks] = xp ? *reinterpret_cast<const bf16x8*>(xp + hoff + hh * 8 + ks * 16) : bf16x8{};
+    for (int ks = 0; ks < N; ++ks)
+      kf[kb][ks] = kp ? *reinterpret_cast<const bf16x8*>(kp + hoff + hh * 8 + ks * 16) : bf16x8{};
   }
+  // V rows of the block's keys into LDS (zeros past the context)
+  for (int i = tid; i < kBwdK * (D / 8); i += kBwdKVThreads) {
+    const int r = i / (D / 8), ch = i % (D / 8);
+    const __bf16* vp = ctx_row<__bf16>(G, kt * kBwdK + r, true, ld);
+    *reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(lds + kV0) + swz(r, ch * 8)) =
+        vp ? *reinterpret_cast<const bf16x8*>(vp + hoff + ch * 8) : bf16x8{};
+  }
+  // the buffer of stage -1 (multiplied by dS = 0 in the first step)
+  for (int i = tid; i < QT / 16; i += kBwdKVThreads)
+    reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB)[i] = bf16x8{};
   // The fragment loads complete before the first transfer: the compiler does
-  // not count the transfers, so a later partial wait would leave it a full
-  // wait before the first use of the fragment in every stage.
+  // not count the transfers.
   wait_vmcnt<0>();
-  f32x16 acc[DB];  // dV^T (A) or dK^T (B)
 #pragma unroll
-  for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
-  f32x16 s[NQB];       // S_t (A) or dP_t (B); zero before the first stage
+  for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) s[qb] = f32x16{};
-  bf16x8 w[NQB][2];    // P_t (A) or dS_{t-1} (B), packed as the B operand of the accumulating product
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) w[qb][0] = w[qb][1] = bf16x8{};
+    for (int ks = 0; ks < N; ++ks) asm volatile("" : "+v"(kf[kb][ks]));
 
-  // Per-lane global offsets of the A waves' transfers (the same every
-  // stage): transfer t = wave NDMA + i covers bytes 1024 (t % (QT / 1024))
-  // of the Q tile (t < QT / 1024) or of the dO tile; logical chunk of the
-  // fixed LDS slot, zero past D.
+  const uint32_t ds_qbytes = static_cast<uint32_t>(G.ds_stages) * (kBwdKS * 64);  // one 32-query block's tiles
+  const char* const ds_head = static_cast<const char*>(G.ds) + static_cast<int64_t>(hl) * G.ds_qblocks * ds_qbytes;
+
+  // This wave's transfers of a stage: 1 KB (4 rows) each, rows 4 (4 (wave & 1)
+  // + i) + lane / 16 of the Q (waves 0, 1) or dO (waves 2, 3) tile, and a row
+  // statistic (waves 0, 1; lanes past the 32 queries read zeros).  Rows past
+  // the range's end arrive as zeros with zero statistics: their P = 1 meets
+  // zero dO rows and dS = 1 (0 - 0) = 0.
   const uint32_t row_bytes = static_cast<uint32_t>(ld) * 2;
-  uint32_t voff[NDMA];
-#pragma unroll
-  for (int i = 0; i < NDMA; ++i) {
-    const int t = (wave & 3) * NDMA + i;
-    const int p = (t % (QT / 1024)) * 1024 + 16 * lane;
-    const int row = p >> 8, phys = (p >> 4) & 15;
-    const int lc = unswz256(row, phys);
-    voff[i] = lc < D / 8 ? row * row_bytes + lc * 16 : kPastEnd;
-  }
+  // Transfer i's offset is that of transfer 0 with its chunk XORed with i, 4 i
+  // rows on (three registers less than one offset per transfer: the kernel
+  // uses all 256).
+  const int row0 = 16 * (wave & 1) + (lane >> 4), lc0 = unswz256(row0, lane & 15);
+  const uint32_t voff0 = lc0 < D / 8 ? row0 * row_bytes + lc0 * 16 : kPastEnd;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  // Stage queries [q0, q0 + BQ) into LDS buffer buf (A waves), all by
-  // direct transfers: the Q (waves 0, 1) or dO (waves 2, 3) tile rows, and
-  // the stage's negated statistics -lse / scale (wave 0) and -rowsum (wave
-  // 1), one dword per lane.  Queries past the end arrive as zero rows with
-  // zero statistics: their P = exp2(0) = 1 meets zero dO rows (no dV
-  // contribution) and dS = 1 (0 - 0) = 0.  Loop-invariant values are kept in registers.
-  static_assert(2 * NDMA * 1024 == QT && BQ == 64, "two A waves per tile, one statistic per lane");
-  const int q_begin = G.q_begin, q_end = G.q_end;
-  const __bf16* const x_head = static_cast<const __bf16*>((wave & 3) < 2 ? a.q : a.d_out) + hoff;
-  const bool stat_wave = wave == 0 || wave == 1;
-  const float* const s_head = (wave == 0 ? a.lse2 : a.dsum) + static_cast<int64_t>(head) * a.n_q;
-  auto issue = [&](int q0, int buf) {
-    const int nv = min(BQ, q_end - q0);
-    const uint32_t bytes = static_cast<uint32_t>(nv - 1) * row_bytes + D * 2;
-    const i32x4 rs = rsrc_of(x_head + static_cast<int64_t>(q0) * ld, bytes);
-    const uint32_t base = lds0 + buf * STB;
-#pragma unroll
-    for (int i = 0; i < NDMA; ++i)
-      dma16(rs, voff[i], __builtin_amdgcn_readfirstlane(base + ((wave & 3) * NDMA + i) * 1024));
-    if (stat_wave)
-      dma4(rsrc_of(s_head + q0, static_cast<uint32_t>(nv) * 4), 4 * lane,
-           __builtin_amdgcn_readfirstlane(base + 2 * QT + wave * BQ * 4));
+  const int q_begin = G.q_begin, nq = G.q_end - G.q_begin, nst = (nq + BQ - 1) / BQ;
+  const __bf16* const x_head =
+      static_cast<const __bf16*>(wave < 2 ? a.q : a.d_out) + hoff + static_cast<int64_t>(q_begin) * ld;
+  const float* const s_head = (wave == 0 ? a.lse2 : a.dsum) + static_cast<int64_t>(head) * a.n_q + q_begin;
+  auto issue = [&](int t, int i) {  // transfer i of stage t (i == NDMA: the statistic); past the last stage zeros
+    const int nv = max(0, min(BQ, nq - t * BQ));
+    const uint32_t base = lds0 + (t & (NBUF - 1)) * STB;
+    if (i < NDMA) {
+      const i32x4 rs = rsrc_of(x_head + static_cast<int64_t>(t) * BQ * ld, nv > 0 ? static_cast<uint32_t>(nv - 1) * row_bytes + D * 2 : 0u);
+      dma16(rs, (voff0 ^ (i * 16)) + i * 4 * row_bytes, __builtin_amdgcn_readfirstlane(base + (wave * NDMA + i) * 1024));
+    } else {
+      // waves 2 and 3 fill the unused part: every wave counts the same transfers
+      dma4(rsrc_of(s_head + t * BQ, static_cast<uint32_t>(nv) * 4), 4 * lane,
+           __builtin_amdgcn_readfirstlane(lds0 + kStat0 + (t & (NBUF - 1)) * kStat + wave * 256));
+    }
   };
-  // Operand offsets in the swizzled tiles (elements), as in the dQ kernel.
+
+  // Lane offsets (elements) of row reads and of transposing reads.
   const int r_rd = swz(n, hh * 8);
   const int t_lane = 4 * (lane >> 5) + ((lane & 15) >> 2);
   const int t_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
@@ -464,184 +484,190 @@ void dkdv_kernel(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int h = 0; h < 2; ++h) t_rd[db][h] = swz(t_lane + 8 * h, db * 32 + t_col);
-  bf16x8* const pex = reinterpret_cast<bf16x8*>(lds + NBUF * STB + pair * PXB) + lane;
-  auto tile = [&](int buf, int which) {  // 0: Q, 1: dO
-    return reinterpret_cast<const __bf16*>(lds + buf * STB + which * QT);
+  const __bf16* const Vw = reinterpret_cast<const __bf16*>(lds + kV0) + wave * 64 * 128;
+  auto tile = [&](int buf, int which) { return reinterpret_cast<const __bf16*>(lds + buf * STB + which * QT); };  // 0: Q, 1: dO
+  auto row_op = [&](const __bf16* x, int ks) { return *reinterpret_cast<const bf16x8*>(x + (r_rd ^ (ks * 16))); };
+  auto tr_op = [&](const __bf16* x, int i) {  // i = (16-row half, channel block)
+    const __bf16* r0 = x + (i / DB) * 16 * 128;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(r0 + t_rd[i % DB][0]));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(r0 + t_rd[i % DB][1]));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  // Matrix-core step of a phase: the accumulating product of the previous
-  // stage (if acc_c: A^T rows of Ys, the wave's w as B operand), then the row
-  // product of the current stage (if row_c: rows of Xs times the wave's
-  // fragment, starting from the statistics at Cs), as one stream of MFMAs
-  // whose LDS operands run kLead ahead.
-  auto mstep = [&](auto acc_c, auto row_c, const __bf16* Ys, const __bf16* Xs, const float* Cs) {
-    constexpr bool kA = decltype(acc_c)::value, kR = decltype(row_c)::value;
-    constexpr int NA = kA ? NQB * 2 * DB : 0;  // (32-row block, 16-row half, column block)
-    constexpr int NR = kR ? NQB * KS : 0;      // (32-row block, k step)
-    constexpr int N = NA + NR;
-    if constexpr (kR) {
+  f32x16 dk[DB][2], dv[DB][2], s[2], dp[2], stat;
+  i32x4 pw[2][2], ds[2][2];  // P_t and dS packed as B operands, [key block][16-query half]
 #pragma unroll
-      for (int qb = 0; qb < NQB; ++qb)
+  for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4 c4 = *reinterpret_cast<const f32x4*>(Cs + qb * 32 + 8 * j + 4 * hh);
+    for (int db = 0; db < DB; ++db) dk[db][kb] = dv[db][kb] = f32x16{};
+    ds[kb][0] = ds[kb][1] = i32x4{};
+  }
+  auto load_stat = [&](int buf, int which) {  // element e: query 8 (e / 4) + 4 hh + e % 4
+    const float* p = reinterpret_cast<const float*>(lds + kStat0 + buf * kStat) + which * 64;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) s[qb][4 * j + i] = c4[i];
+    for (int j = 0; j < 4; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(p + 8 * j + 4 * hh);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) stat[4 * j + i] = v[i];
+    }
+  };
+  auto pack = [](float x, float y) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(int, bf16x2{static_cast<__bf16>(x), static_cast<__bf16>(y)});
+  };
+  // Pair x (of 16) of the lane's 32 elements: key block x / 8, elements e, e + 1.
+  // P stays in s in fp32 for dS.
+  auto p_pair = [&](int x) {
+    const int kb = x >> 3, e = (x & 7) * 2;
+    s[kb][e] = __builtin_amdgcn_exp2f(kQS ? s[kb][e] : s[kb][e] * c);
+    s[kb][e + 1] = __builtin_amdgcn_exp2f(kQS ? s[kb][e + 1] : s[kb][e + 1] * c);
+    pw[kb][e >> 3][(e & 7) >> 1] = pack(s[kb][e], s[kb][e + 1]);
+  };
+  auto ds_pair = [&](int x) {
+    const int kb = x >> 3, e = (x & 7) * 2;
+    ds[kb][e >> 3][(e & 7) >> 1] = pack(s[kb][e] * dp[kb][e], s[kb][e + 1] * dp[kb][e + 1]);
+  };
+  auto ds_store = [&](int t, int kb, int h) {  // stage t's dS of one key block and tile half
+    const i32x4 rd = rsrc_of(ds_head + static_cast<int64_t>(max(t, 0)) * ds_qbytes, t >= 0 && t < nst ? ds_qbytes : 0u);
+    if (h == 0)
+      bstore16_nt<0>(ds[kb][0], rd, ds_voff[kb], 0);
+    else
+      bstore16_nt<kBwdKS * 32>(ds[kb][1], rd, ds_voff[kb], 0);
+  };
+  // Runs f(x) for the pairs x that slot j of n (of which the first does
+  // nothing: the pairs' inputs may still be in the matrix core) has to do.
+  auto spread = [](auto J, auto n_c, auto pairs_c, auto&& f) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value, n = decltype(n_c)::value, pairs = decltype(pairs_c)::value;
+    if constexpr (j > 0) {
+      constexpr int x0 = ((j - 1) * pairs + n - 2) / (n - 1), x1 = (j * pairs + n - 2) / (n - 1);
+      if constexpr (x0 < x1) f(x0);
+      if constexpr (x0 + 1 < x1) f(x0 + 1);
+      if constexpr (x0 + 2 < x1) f(x0 + 2);
+      static_assert(x1 - x0 <= 3, "pairs per slot");
+    }
+  };
+
+  bf16x8 ring[kLead], vring[2][2];
+  // Operand of chunk i (0 .. 4 N - 1; 4 N .. : the next step's) of a step on buffer B.
+  auto operand = [&](auto B, int i) {
+    constexpr int cur = decltype(B)::value, prev = (cur + NBUF - 1) % NBUF, next = (cur + 1) % NBUF;
+    if (i < N) return row_op(tile(cur, 0), i);
+    if (i < 2 * N) return tr_op(tile(prev, 0), i - N);
+    if (i < 3 * N) return row_op(tile(cur, 1), i - 2 * N);
+    if (i < 4 * N) return tr_op(tile(cur, 1), i - 3 * N);
+    return row_op(tile(next, 0), i - 4 * N);
+  };
+  auto v_op = [&](int ks, int kb) { return row_op(Vw + kb * 32 * 128, ks); };
+
+  auto step = [&](auto B, int t) __attribute__((always_inline)) {
+    constexpr int cur = decltype(B)::value, next = (cur + 1) % NBUF;
+    for_constants(std::make_integer_sequence<int, 4 * N>{}, [&](auto I) __attribute__((always_inline)) {
+      constexpr int i = decltype(I)::value, ph = i / N, j = i % N;
+      if (i == 3 * N) {
+        // stage t + 1 has arrived: younger than its transfers (in A of the
+        // previous step) are that step's four stores, stage t + 2's transfers
+        // and this step's four stores
+        // (operand reads stay in flight across the barrier: no buffer they
+        // read is overwritten before the next one)
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NDMA + 1 + 8) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const bf16x8 av = ring[i % kLead];
+      for_constants(std::make_integer_sequence<int, 2>{}, [&](auto KB) __attribute__((always_inline)) {
+        constexpr int kb = decltype(KB)::value, sl = 2 * j + kb;  // slot sl of the phase's 2 N
+        if constexpr (ph == 0 && j == 0)
+          mfma_first(s[kb], av, kf[kb][0], stat);
+        else if constexpr (ph == 0)
+          mfma_v(s[kb], av, kf[kb][j]);
+        else if constexpr (ph == 1)
+          mfma_a(dk[j % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][j / DB]));
+        else if constexpr (ph == 2 && j == 0)
+          mfma_first(dp[kb], av, vring[0][kb], stat);
+        else if constexpr (ph == 2)
+          mfma_v(dp[kb], av, vring[j & 1][kb]);
+        else
+          mfma_a(dv[j % DB][kb], av, __builtin_bit_cast(bf16x8, pw[kb][j / DB]));
+        if (kb == 0) {
+          // operands ahead: the last chunks of a step read the next step's
+          // stage, after the barrier
+          ring[i % kLead] = operand(B, i + kLead);
+          if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][0] = v_op(i + 2 - 2 * N, 0);
+        } else {
+          if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][1] = v_op(i + 2 - 2 * N, 1);
+          if (ph == 1 && j == N - 2) load_stat(cur, 1);
+          if (ph == 3 && j == N - 2) load_stat(next, 0);
+        }
+        if constexpr (ph == 0) {
+          if (sl <= NDMA) issue(t + 2, sl);  // before the stores: the wait above counts on it
+          if (N == 4 && sl == 2 * N - 2) {
+            ds_store(t - 1, 0, 0);
+            ds_store(t - 1, 0, 1);
+          }
+          if (N == 4 && sl == 2 * N - 1) {
+            ds_store(t - 1, 1, 0);
+            ds_store(t - 1, 1, 1);
+          }
+          if (N > 4 && sl >= 2 * N - 8 && sl % 2 == 0) ds_store(t - 1, (sl - (2 * N - 8)) / 4, (sl - (2 * N - 8)) / 2 % 2);
+        } else if constexpr (ph == 3) {
+          spread(std::integral_constant<int, sl>{}, std::integral_constant<int, 2 * N>{}, std::integral_constant<int, 16>{}, ds_pair);
+        } else {
+          spread(std::integral_constant<int, (ph - 1) * 2 * N + sl>{}, std::integral_constant<int, 4 * N>{},
+                 std::integral_constant<int, 16>{}, p_pair);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+    // dS is due here, not in the next step's block
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(ds[kb][h]));
+  };
+
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i <= NDMA; ++i) issue(t, i);
+  wait_vmcnt<0>();
+  __syncthreads();
+  load_stat(0, 0);
+#pragma unroll
+  for (int i = 0; i < kLead; ++i) ring[i] = operand(I0{}, i);
+  // The step after the last one finishes dK of the last stage and stores its
+  // dS; its own stage, and those that fill the round, are all zeros.
+  for (int t = 0; t <= nst; t += NBUF) {
+    step(I0{}, t);
+    step(I1{}, t + 1);
+    step(I2{}, t + 2);
+    step(I3{}, t + 3);
+  }
+  wait_vmcnt<0>();  // no transfer into this block's LDS outlives it
+  // the last products have left the matrix core before the accumulators are read
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const int key = key0 + kb * 32;
+    if (key < G.n_kv) {
+      const int64_t off = static_cast<int64_t>(key) * ld + hoff + 4 * hh;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          f32x4 k4, v4;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            k4[i] = dk[db][kb][4 * jj + i] * a.scale;
+            v4[i] = dv[db][kb][4 * jj + i];
+          }
+          *reinterpret_cast<f32x4*>(G.dk_ctx + off + db * 32 + 8 * jj) = k4;
+          *reinterpret_cast<f32x4*>(G.dv_ctx + off + db * 32 + 8 * jj) = v4;
         }
     }
-    auto operand = [&](int i) -> bf16x8 {
-      if (i < NA) {
-        const int qb = i / (2 * DB), cc = (i / DB) & 1, db = i % DB;
-        const __bf16* r0 = Ys + (qb * 32 + cc * 16) * 128;
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(r0 + t_rd[db][0]));
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(r0 + t_rd[db][1]));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-      const int j = i - NA, qb = j / KS, ks = j % KS;
-      return *reinterpret_cast<const bf16x8*>(Xs + qb * 32 * 128 + (r_rd ^ (ks * 16)));
-    };
-    bf16x8 ring[kLead];
-#pragma unroll
-    for (int i = 0; i < kLead; ++i)
-      if (i < N) ring[i] = operand(i);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const bf16x8 av = ring[i % kLead];
-      if (i < NA) {
-        const int qb = i / (2 * DB), cc = (i / DB) & 1, db = i % DB;
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, w[qb][cc], acc[db], 0, 0, 0);
-      } else {
-        const int j = i - NA, qb = j / KS, ks = j % KS;
-        s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, xf[ks], s[qb], 0, 0, 0);
-      }
-      if (i + kLead < N) ring[i % kLead] = operand(i + kLead);
-    }
-    auto read_group = [&](int i) {  // an A^T operand is two LDS reads, a row operand one
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      if (i < NA) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    };
-    if (kR) __builtin_amdgcn_sched_group_barrier(0x100, 4 * NQB, 0);  // the statistics
-#pragma unroll
-    for (int i = 0; i < (N < kLead ? N : kLead); ++i) read_group(i);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i + kLead < N) read_group(i + kLead);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  // Element e of a 32x32 accumulator in this layout holds query
-  // qb*32 + 8(e/4) + 4hh + e%4 of the lane's key.
-  // A: P_t = exp2(S'_t c) (S' = S - lse / scale) into w and into the pair's
-  // LDS block.
-  auto softmax_a = [&]() {
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        w[qb][e >> 3][e & 7] = static_cast<__bf16>(__builtin_amdgcn_exp2f(kQS ? s[qb][e] : s[qb][e] * c));
-      pex[(qb * 2) * 64] = w[qb][0];
-      pex[(qb * 2 + 1) * 64] = w[qb][1];
-    }
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(w[qb][h]));
-  };
-  // B: dS = P dP' (dP' = dP - rowsum) of stage ts into w, and to the dS
-  // tiles of the stage's 32-query blocks 2 ts + qb for the dQ kernel.  Stage
-  // -1 (the first phase) computes exact zeros from the zeroed P block and
-  // dP registers, and its buffer range is empty, so nothing is stored.
-  auto softmax_b = [&](int ts) {
-    const i32x4 rd = rsrc_of(ds_head + static_cast<int64_t>(NQB * max(ts, 0)) * G.ds_stages * (kBwdKS * 32),
-                             ts >= 0 ? NQB * ds_qbytes : 0u);
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      const bf16x8 p0 = pex[(qb * 2) * 64], p1 = pex[(qb * 2 + 1) * 64];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float p = static_cast<float>((e < 8 ? p0 : p1)[e & 7]);
-        w[qb][e >> 3][e & 7] = static_cast<__bf16>(p * s[qb][e]);
-      }
-      bstore16_nt<0>(__builtin_bit_cast(i32x4, w[qb][0]), rd, ds_voff, qb * ds_qbytes);
-      bstore16_nt<kBwdKS * 32>(__builtin_bit_cast(i32x4, w[qb][1]), rd, ds_voff, qb * ds_qbytes);
-    }
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(w[qb][h]));
-  };
-
-  // One matrix-core step for every stage and both roles (one instantiation
-  // keeps the register allocation tight): in the first stage the
-  // accumulating product multiplies the zeroed buffer of stage -1 by w = 0,
-  // adding exact zeros; in the stage after the last, the row product's
-  // result is never used.  A issues stage t + 2 at the start of its VALU
-  // phase 2t + 1, into the buffer of stage t - 2 (last read in phase 2t - 1),
-  // and ends that phase once stage t + 1 has arrived.
-  using T_ = std::true_type;
-  const int nst = (q_end - q_begin + BQ - 1) / BQ;
-  {
-    bf16x8* z = reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB);
-#pragma unroll
-    for (int i = 0; i < 2 * QT / 16 / kBwdKVThreads; ++i) z[tid + i * kBwdKVThreads] = bf16x8{};
-    bf16x8* zp = reinterpret_cast<bf16x8*>(lds + NBUF * STB);  // the P exchange blocks
-    static_assert(4 * PXB % (16 * kBwdKVThreads) == 0, "P blocks zeroed whole");
-#pragma unroll
-    for (int i = 0; i < 4 * PXB / 16 / kBwdKVThreads; ++i) zp[tid + i * kBwdKVThreads] = bf16x8{};
-  }
-  // this wave's transfers of one stage (the stage issued last may stay in flight)
-  auto wait_all_but_last = [&]() {
-    if (stat_wave)
-      wait_vmcnt<NDMA + 1>();
-    else
-      wait_vmcnt<NDMA>();
-  };
-  if (role == 0) {
-    issue(q_begin, 0);
-    if (nst > 1) {
-      issue(q_begin + BQ, 1);
-      wait_all_but_last();
-    } else {
-      wait_vmcnt<0>();
-    }
-  }
-  __syncthreads();
-  // Phase ph = 2t + r: role r runs the matrix-core step of stage t, the
-  // other role its VALU work.
-  for (int ph = 0; ph < 2 * nst + 2; ++ph) {
-    const int t = ph >> 1, cur = t % NBUF, prev = (t + NBUF - 1) % NBUF;  // buffers of stages t, t - 1
-    if ((ph & 1) == role) {
-      __builtin_amdgcn_s_setprio(2);
-      mstep(T_{}, T_{}, tile(prev, 1 - role), tile(cur, role),
-            reinterpret_cast<const float*>(lds + cur * STB + 2 * QT) + role * BQ);
-      __builtin_amdgcn_s_setprio(0);
-    } else if (role == 0) {
-      if (t + 2 < nst) issue(q_begin + (t + 2) * BQ, (t + 2) % NBUF);
-      if (t < nst) softmax_a();
-      if (t + 2 < nst)
-        wait_all_but_last();
-      else
-        wait_vmcnt<0>();
-    } else {
-      softmax_b(t - 1);
-    }
-    __syncthreads();
-  }
-
-  if (k_ok) {
-    float* dst = role == 0 ? G.dv_ctx : G.dk_ctx;
-    const float sc = role == 0 ? 1.f : a.scale;
-    const int64_t off = static_cast<int64_t>(key) * ld + hoff + 4 * hh;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        f32x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = acc[db][4 * jj + i] * sc;
-        *reinterpret_cast<f32x4*>(dst + off + db * 32 + 8 * jj) = v;
-      }
   }
 }
 

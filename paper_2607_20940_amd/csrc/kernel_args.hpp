@@ -81,9 +81,10 @@ constexpr int64_t split_record_floats(int head_dim) { return 32 * static_cast<in
 constexpr int kBwdQ = 256;     // dQ kernel: queries per block (8 waves x 32)
 constexpr int kBwdQThreads = 512;   // dQ kernel: 8 waves, two per SIMD
 constexpr int kBwdKS = 64;     // dQ kernel: keys per LDS stage (and per dS tile)
-constexpr int kBwdK = 128;     // dK/dV kernel: keys per block (4 wave pairs x 32)
-constexpr int kBwdKVThreads = 512;  // dK/dV kernel: 8 waves, two per SIMD
-constexpr int kBwdQS = 64;     // dK/dV kernel: queries per LDS stage
+constexpr int kBwdK = 256;     // dK/dV kernel: keys per block (4 waves x 64)
+constexpr int kBwdKVThreads = 256;  // dK/dV kernel: 4 waves, one per SIMD
+constexpr int kBwdQS = 64;     // dS tiles: queries are rounded up to this
+constexpr int kBwdStage = 32;  // dK/dV kernel: queries per LDS stage
 constexpr int64_t kBwdDsBudget = int64_t(8) << 30;  // bytes of dS tiles held at once (whole heads, at least one)
 constexpr int kBwdF32 = 32;    // fp32 kernels: queries (dQ) or keys (dK, dV) per block
 constexpr int kDotThreads = 256;

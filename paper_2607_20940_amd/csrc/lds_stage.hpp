@@ -81,10 +81,12 @@ __device__ inline void dma16_soff(i32x4 rsrc, uint32_t voff, uint32_t soff, uint
 
 // Store of lane i's 16 bytes at buffer offset voff + soff + IMM
 // (buffer_store_dwordx4, non-temporal: data that another kernel reads once);
-// lanes whose offset is past the buffer's range store nothing.
+// lanes whose offset is past the buffer's range store nothing.  The s_nop is
+// the wait state between a store of more than 8 bytes and a write of its data
+// registers, which the compiler does not see to for inline asm.
 template <int IMM>
 __device__ inline void bstore16_nt(i32x4 data, i32x4 rsrc, uint32_t voff, uint32_t soff) {
-  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen offset:%4 nt"
+  asm volatile("buffer_store_dwordx4 %0, %1, %2, %3 offen offset:%4 nt\n\ts_nop 0"
                :: "v"(data), "v"(voff), "s"(rsrc), "s"(soff), "n"(IMM) : "memory");
 }
 
