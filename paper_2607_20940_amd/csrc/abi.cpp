@@ -739,6 +739,8 @@ mssa_status mssa_backward(mssa_plan plan, const void* q_win, const void* k_sink,
     a.n_groups = G;
     set_score_scales(p, a.scale, a.scale_log2e);
     a.q_prescaled = p.q_prescaled ? 1 : 0;
+    a.dq_splits = p.dq_splits;
+    a.dq_partial = p.dq_splits > 1 ? reinterpret_cast<float*>(ws + p.partial_off) : nullptr;
     const int qb = bf16 ? mssa::kBwdQ : mssa::kBwdF32, kb = bf16 ? mssa::kBwdK : mssa::kBwdF32;
     const KvSources src{k_sink, v_sink, k_hist, v_hist, nullptr, nullptr, k_win, v_win, ws};
     int gi = 0;

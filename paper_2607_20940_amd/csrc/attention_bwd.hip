@@ -138,7 +138,10 @@ __device__ inline int swz(int row, int col) { return swz256(row, col); }
 // (keys) of 32 query positions, which become the accumulator's columns.
 // Position p of a tile row holds query 8 ((p % 16) / 4) + 4 (p / 16) + p % 4
 // of the 32-query block: the order in which the dK/dV kernel's lanes hold
-// them.
+// them.  A block's chain of stages is bound by their latency (about 0.85 us
+// each), so where the blocks leave CUs idle the context is split over
+// dq_splits of them (6 heads of 64 on 17 x 23: 36 blocks, 45 us; with 7 splits
+// 10 us and 5 us for the sum).
 template <int D>
 __global__ __launch_bounds__(kBwdQThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dq_kernel(BwdArgs a) {
@@ -157,7 +160,8 @@ void dq_kernel(BwdArgs a) {
   static_assert(NK * 1024 * NW == KT && NW * 32 == kBwdQ && BN % 32 == 0 && NDS % 2 == 0, "stage shape");
   __shared__ __attribute__((aligned(16))) char lds[3 * STB];
 
-  const int b = blockIdx.x;
+  // dq_splits > 1: block b takes context split b / dq_blocks
+  const int sp = blockIdx.x / a.dq_blocks, b = blockIdx.x - sp * a.dq_blocks;
   int g = 0;
   while (g + 1 < a.n_groups && b >= a.groups[g + 1].dq_block_begin) ++g;
   const BwdGroupArgs& G = a.groups[g];
@@ -180,6 +184,8 @@ void dq_kernel(BwdArgs a) {
   const int nr = G.n_runs;
   int nst = 0;
   for (int r = 0; r < nr; ++r) nst += (G.runs[r].n_tok + BN - 1) / BN;
+  const int st0 = static_cast<int>(static_cast<int64_t>(nst) * sp / a.dq_splits);  // this split's first stage
+  nst = static_cast<int>(static_cast<int64_t>(nst) * (sp + 1) / a.dq_splits) - st0;
   struct Stream {
     const __bf16* k;
     int left;  // tokens of the current run from k on
@@ -215,7 +221,7 @@ void dq_kernel(BwdArgs a) {
     voff[i] = lc < D / 8 ? row * row_bytes + lc * 16 : kPastEnd;
   }
   const __bf16* const ds_wave = static_cast<const __bf16*>(G.ds) +
-      (static_cast<int64_t>(hl) * G.ds_qblocks + (wave_ok ? qb : 0)) * G.ds_stages * (BN * 32);
+      ((static_cast<int64_t>(hl) * G.ds_qblocks + (wave_ok ? qb : 0)) * G.ds_stages + st0) * (BN * 32);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   auto issue = [&](const Stream& s, int st, int buf) {
     const int nv = min(s.left, BN);
@@ -274,7 +280,16 @@ void dq_kernel(BwdArgs a) {
   };
 
   Stream ls;
-  seek(ls, 0);
+  {
+    int r = 0, skip = st0;
+    while (r < nr && skip >= (G.runs[r].n_tok + BN - 1) / BN) {
+      skip -= (G.runs[r].n_tok + BN - 1) / BN;
+      ++r;
+    }
+    seek(ls, r);
+    ls.k += skip * tile_step;
+    ls.left -= skip * BN;
+  }
   if (nst > 0) issue(ls, 0, 0);
   if (nst > 1) {
     step(ls);
@@ -297,6 +312,22 @@ void dq_kernel(BwdArgs a) {
     __syncthreads();
   }
 
+  if (a.dq_splits > 1) {
+    // this split's sum, in fp32 where dq_sum_kernel finds it
+    if (wave_ok && q_row < G.q_end) {
+      float* op = a.dq_partial + (static_cast<int64_t>(sp) * a.n_q + q_row) * ld + hoff + 4 * hh;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          f32x4 v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = acc[db][4 * jj + i];
+          *reinterpret_cast<f32x4*>(op + db * 32 + 8 * jj) = v;
+        }
+    }
+    return;
+  }
   if (wave_ok && q_row < G.q_end) {
     __bf16* op = static_cast<__bf16*>(a.dq) + static_cast<int64_t>(q_row) * ld + hoff + 4 * hh;
 #pragma unroll
@@ -309,6 +340,19 @@ void dq_kernel(BwdArgs a) {
         *reinterpret_cast<bf16x4*>(op + db * 32 + 8 * jj) = v;
       }
   }
+}
+
+// dQ from the fp32 sums of the context splits, split 0 first.
+__global__ __launch_bounds__(kDotThreads) void dq_sum_kernel(BwdArgs a) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * kDotThreads + threadIdx.x, n = a.n_q * a.ld / 4;
+  if (i >= n) return;
+  const f32x4* p = reinterpret_cast<const f32x4*>(a.dq_partial) + i;
+  f32x4 s = p[0];
+  for (int k = 1; k < a.dq_splits; ++k) s += p[k * n];
+  bf16x4 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = static_cast<__bf16>(s[j] * a.scale);
+  reinterpret_cast<bf16x4*>(a.dq)[i] = v;
 }
 
 // ------------------------------------------------------------------ bf16: dK, dV
@@ -408,7 +452,6 @@ void dkdv_kernel(BwdArgs a) {
   // them), slot and the lane's 8 queries of each tile half.  Keys past the
   // context point past the range: the range check drops their stores.
   uint32_t ds_voff[2];
-  bf16x8 kf[2][N];
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int key = key0 + kb * 32;
@@ -420,29 +463,7 @@ void dkdv_kernel(BwdArgs a) {
       ++r;
     }
     ds_voff[kb] = ok ? static_cast<uint32_t>((st + j / kBwdKS) * (kBwdKS * 64) + (j % kBwdKS) * 32 + 16 * hh) : kPastEnd;
-    const __bf16* kp = ctx_row<__bf16>(G, key, false, ld);
-#pragma unroll
-    for (int ks = 0; ks < N; ++ks)
-      kf[kb][ks] = kp ? *reinterpret_cast<const bf16x8*>(kp + hoff + hh * 8 + ks * 16) : bf16x8{};
   }
-  // V rows of the block's keys into LDS (zeros past the context)
-  for (int i = tid; i < kBwdK * (D / 8); i += kBwdKVThreads) {
-    const int r = i / (D / 8), ch = i % (D / 8);
-    const __bf16* vp = ctx_row<__bf16>(G, kt * kBwdK + r, true, ld);
-    *reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(lds + kV0) + swz(r, ch * 8)) =
-        vp ? *reinterpret_cast<const bf16x8*>(vp + hoff + ch * 8) : bf16x8{};
-  }
-  // the buffer of stage -1 (multiplied by dS = 0 in the first step)
-  for (int i = tid; i < QT / 16; i += kBwdKVThreads)
-    reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB)[i] = bf16x8{};
-  // The fragment loads complete before the first transfer: the compiler does
-  // not count the transfers.
-  wait_vmcnt<0>();
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int ks = 0; ks < N; ++ks) asm volatile("" : "+v"(kf[kb][ks]));
-
   const uint32_t ds_qbytes = static_cast<uint32_t>(G.ds_stages) * (kBwdKS * 64);  // one 32-query block's tiles
   const char* const ds_head = static_cast<const char*>(G.ds) + static_cast<int64_t>(hl) * G.ds_qblocks * ds_qbytes;
 
@@ -474,6 +495,43 @@ void dkdv_kernel(BwdArgs a) {
            __builtin_amdgcn_readfirstlane(lds0 + kStat0 + (t & (NBUF - 1)) * kStat + wave * 256));
     }
   };
+
+  // Everything a block starts with is requested at once: the first two stages,
+  // the K fragments and the V rows (zeros past the context), kept in registers
+  // until they are all there.
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i <= NDMA; ++i) issue(t, i);
+  bf16x8 kf[2][N];
+  {
+    constexpr int CH = D / 8, RP = kBwdKVThreads / CH, NV = kBwdK / RP;  // 16-byte chunks per row, rows per pass, passes
+    bf16x8 vrow[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const __bf16* vp = ctx_row<__bf16>(G, kt * kBwdK + i * RP + tid / CH, true, ld);
+      vrow[i] = vp ? *reinterpret_cast<const bf16x8*>(vp + hoff + tid % CH * 8) : bf16x8{};
+    }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const __bf16* kp = ctx_row<__bf16>(G, key0 + kb * 32, false, ld);
+#pragma unroll
+      for (int ks = 0; ks < N; ++ks)
+        kf[kb][ks] = kp ? *reinterpret_cast<const bf16x8*>(kp + hoff + hh * 8 + ks * 16) : bf16x8{};
+    }
+    // the buffer of stage -1 (multiplied by dS = 0 in the first step)
+    for (int i = tid; i < QT / 16; i += kBwdKVThreads)
+      reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB)[i] = bf16x8{};
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      *reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(lds + kV0) + swz(i * RP + tid / CH, tid % CH * 8)) = vrow[i];
+  }
+  wait_vmcnt<0>();  // the transfers too, which the compiler does not count
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int ks = 0; ks < N; ++ks) asm volatile("" : "+v"(kf[kb][ks]));
+  __syncthreads();
 
   // Lane offsets (elements) of row reads and of transposing reads.
   const int r_rd = swz(n, hh * 8);
@@ -628,26 +686,39 @@ void dkdv_kernel(BwdArgs a) {
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int i = 0; i <= NDMA; ++i) issue(t, i);
-  wait_vmcnt<0>();
-  __syncthreads();
   load_stat(0, 0);
 #pragma unroll
   for (int i = 0; i < kLead; ++i) ring[i] = operand(I0{}, i);
-  // The step after the last one finishes dK of the last stage and stores its
-  // dS; its own stage, and those that fill the round, are all zeros.
-  for (int t = 0; t <= nst; t += NBUF) {
+  // Stages past the last one, which fill the round, are all zeros (a way out
+  // between the steps made the compiler move the accumulators about).
+  int t = 0;
+  do {  // a group has queries
     step(I0{}, t);
     step(I1{}, t + 1);
     step(I2{}, t + 2);
     step(I3{}, t + 3);
+    t += NBUF;
+  } while (t < nst);
+  // dS of the round's last stage, and its dK
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) ds_store(t - 1, kb, h);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bf16x8 av = tr_op(tile(NBUF - 1, 0), i);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) mfma_a(dk[i % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][i / DB]));
   }
   wait_vmcnt<0>();  // no transfer into this block's LDS outlives it
   // the last products have left the matrix core before the accumulators are read
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      asm volatile("s_nop 15" : "+a"(dk[db][kb]));
+      asm volatile("s_nop 15" : "+a"(dv[db][kb]));
+    }
 
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
@@ -752,10 +823,18 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
     if (e != hipSuccess) return e;
   }
   if (dq_blocks > 0) {
+    BwdArgs d = a;
+    d.dq_blocks = dq_blocks;
+    const int64_t grid = static_cast<int64_t>(dq_blocks) * d.dq_splits;
+    if (d.dq_splits < 1 || grid > 0x7fffffff || (d.dq_splits > 1 && !d.dq_partial)) return hipErrorInvalidValue;
     if (head_dim == 128)
-      hipLaunchKernelGGL(dq_kernel<128>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
+      hipLaunchKernelGGL(dq_kernel<128>, dim3(static_cast<uint32_t>(grid)), dim3(kBwdQThreads), 0, stream, d);
     else
-      hipLaunchKernelGGL(dq_kernel<64>, dim3(dq_blocks), dim3(kBwdQThreads), 0, stream, a);
+      hipLaunchKernelGGL(dq_kernel<64>, dim3(static_cast<uint32_t>(grid)), dim3(kBwdQThreads), 0, stream, d);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || d.dq_splits == 1) return e;
+    const int64_t n = (d.n_q * d.ld / 4 + kDotThreads - 1) / kDotThreads;
+    hipLaunchKernelGGL(dq_sum_kernel, dim3(static_cast<uint32_t>(n)), dim3(kDotThreads), 0, stream, d);
     return hipGetLastError();
   }
   return hipSuccess;

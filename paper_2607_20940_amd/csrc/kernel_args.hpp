@@ -121,6 +121,9 @@ struct BwdArgs {
   float scale;              // softmax scale
   float scale_log2e;
   int32_t q_prescaled;      // queries arrive multiplied by scale * log2(e)
+  int32_t dq_splits;        // bf16 dQ kernel: blocks that share the context of 256 queries
+  int32_t dq_blocks;        // its blocks per split (set by the launcher)
+  float* dq_partial;        // dq_splits > 1: fp32 sums [dq_splits][n_q][ld]
   BwdGroupArgs groups[kMaxGroups];  // longest query range first
 };
 static_assert(sizeof(BwdArgs) <= 4096, "kernel argument block");

@@ -333,6 +333,19 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     if (p.n_ranges > 1) p.range_table_off = ws + p.partial_bytes - align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
   }
   p.sched = make_schedule(p, run_tok);
+  if (d.dtype == MSSA_BF16) {
+    // dQ of a layer with few 256-query blocks: splits of at least six 64-key
+    // stages of the longest context.  Their sums may take the place of the
+    // forward's records.
+    int64_t stages = 0;
+    for (int64_t n : run_tok[p.order.front()]) stages += (n + kBwdKS - 1) / kBwdKS;
+    const int64_t s = std::max<int64_t>(1, std::min({slots / n_items, stages / 6, int64_t{8}}));
+    const int64_t bytes = s > 1 ? align256(s * p.n_q * p.ld * 4) : 0;
+    if (s > 1 && !p.hist_ring && (room < 0 || std::max(p.partial_bytes, bytes) <= room)) {
+      p.dq_splits = static_cast<int32_t>(s);
+      p.partial_bytes = std::max(p.partial_bytes, bytes);
+    }
+  }
   ws += p.partial_bytes;
   p.workspace_bytes = ws;
 
@@ -375,6 +388,7 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     // whole heads per chunk within the budget, at least one
     p.bwd_ds_heads = static_cast<int32_t>(
         std::max<int64_t>(1, std::min<int64_t>(d.num_heads, kBwdDsBudget / std::max<int64_t>(1, per_head))));
+    if (p.bwd_ds_heads < d.num_heads) p.dq_splits = 1;  // the splits' sums are added up once, for all heads
     for (int g = 0; g < G; ++g) {
       p.bwd_ds_off[g] = ws;
       ws += align256(static_cast<int64_t>(p.bwd_ds_heads) * p.bwd_ds_qblocks[g] * p.bwd_ds_stages[g] * kBwdKS * 32 * 2);

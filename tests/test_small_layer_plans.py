@@ -9,9 +9,9 @@ from paper_2607_20940_amd import mssa
 SCRATCH = mssa.MSSA_NOALLOC_SCRATCH_BYTES
 
 
-def _plan(hist, dtype, blocks=0, heads=1, grid=64):
+def _plan(hist, dtype, blocks=0, heads=1, grid=64, flags=0):
     desc = dict(num_states=2, scales=[1, 2], grid_h=grid, grid_w=grid, frames_per_state=1, sink_frames=0,
-                hist_frames=hist, num_heads=heads, head_dim=128, dtype=dtype)
+                hist_frames=hist, num_heads=heads, head_dim=128, dtype=dtype, flags=flags)
     return mssa.mssa_plan_create_ex(desc, blocks)
 
 
@@ -32,9 +32,10 @@ def test_long_history_of_one_head_fits_the_scratch(dtype):
 
 
 def test_given_attention_blocks_are_kept():
-    """A given number of blocks is the number of ranges, whatever the layer."""
+    """A given number of blocks is the number of ranges, whatever the layer
+    (a plan without a backward, whose sums share the records' place)."""
     rec = 2 * 256 * (128 + 2) * 4
     for blocks in (2, 7, 97):
-        base = _plan(4, "bf16", 1, grid=32).info()["workspace_bytes"]
-        ws = _plan(4, "bf16", blocks, grid=32).info()["workspace_bytes"]
+        base = _plan(4, "bf16", 1, grid=32, flags=mssa.MSSA_PLAN_POOLED_HIST_RING).info()["workspace_bytes"]
+        ws = _plan(4, "bf16", blocks, grid=32, flags=mssa.MSSA_PLAN_POOLED_HIST_RING).info()["workspace_bytes"]
         assert ws == base + blocks * rec + ((blocks + 1) * 8 + 255) // 256 * 256
