@@ -356,7 +356,8 @@ mssa_status mssa_qkv_project_scaled(int64_t n_tokens, int32_t hidden, const void
  *   k_ring, v_ring   device ring buffers (must not overlap k_win / v_win)
  *   ring_head, ring_count  host in/out; 0 <= count <= cap, 0 <= head < cap,
  *                    head == 0 unless count == cap
- * Enqueues device-to-device copies on `stream`; MSSA_ERR_UNSUPPORTED if
+ * Enqueues the copies on `stream` (one kernel for 16-byte aligned tensors,
+ * device-to-device copies for others); MSSA_ERR_UNSUPPORTED if
  * scales[0] != 1 or ring_cap_frames < frames_per_state. */
 mssa_status mssa_hist_append(mssa_plan plan, const void* k_win, const void* v_win, void* k_ring,
                              void* v_ring, int32_t ring_cap_frames, int32_t* ring_head,
