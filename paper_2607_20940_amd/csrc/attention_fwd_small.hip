@@ -13,8 +13,9 @@
 // the scores; two waves share a SIMD and cover each other's waits.  The price
 // is K/V read once per 32 queries instead of once per 256, so the L2 bounds it
 // and the dispatch (small_layer_splits in plan.cpp) keeps it to small layers.
-// Measured, pass: 2 heads of 128 on a 10 x 13 grid 55.9 -> 18.4 us, 6 heads of
-// 64 on 17 x 23 79.8 -> 25.7 us.
+// Measured, pass: 2 heads of 128 on a 10 x 13 grid 55.9 -> 18.3 us, 6 heads of
+// 64 on 17 x 23 79.8 -> 24.9 us (25.8 with the scale applied to every score
+// before the maximum and the mask on every tile).
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
@@ -71,6 +72,7 @@ void fwd_small_kernel(FwdArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t ld = a.ld, hoff = static_cast<int64_t>(head) * D;
   const uint32_t rb = static_cast<uint32_t>(ld) * 2;
+  const float c = a.scale_log2e;
 
   // Tiles of this wave: t, t + 8, .. below t1, each inside one run.
   int nt = 0;
@@ -155,14 +157,15 @@ void fwd_small_kernel(FwdArgs a) {
       settle();
       issue_k();
     }
-    float mx = -INFINITY;
+    if (valid < 32) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int key = 8 * (e >> 2) + 4 * hh + (e & 3);
-      s[e] = key < valid ? s[e] * a.scale_log2e : -INFINITY;
-      mx = fmaxf(mx, s[e]);
+      for (int e = 0; e < 16; ++e)
+        if (8 * (e >> 2) + 4 * hh + (e & 3) >= valid) s[e] = -INFINITY;
     }
-    mx = fmaxf(mx, other_half(mx));
+    float mx = fmaxf(s[0], s[1]);
+#pragma unroll
+    for (int e = 2; e < 16; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
+    mx = fmaxf(mx, other_half(mx)) * c;  // the scale is positive
     if (__any(mx > m + kRescaleLog2 || (m == -INFINITY && mx > m))) {
       const float mn = fmaxf(m, mx);
       const float alpha = mn == m ? 1.f : __builtin_amdgcn_exp2f(m - mn);
@@ -176,7 +179,7 @@ void fwd_small_kernel(FwdArgs a) {
     float ls[2] = {0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const float p = __builtin_amdgcn_exp2f(s[e] - ms);
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -ms));
       ls[e & 1] += p;
       pb[e >> 3][e & 7] = static_cast<__bf16>(p);
     }
