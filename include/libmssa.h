@@ -149,8 +149,9 @@ mssa_status mssa_plan_create(const mssa_plan_desc* desc, mssa_plan* out);
  * attention_blocks equal shares, one per block; a share may end inside an
  * item, whose pieces are then merged in a fixed order.  attention_blocks ==
  * 0 takes one block per resident slot of the current device (512 without a
- * device), as mssa_plan_create does; fewer leaves compute units to other
- * streams, more runs in several waves.  The plan's workspace size depends on
+ * device), as mssa_plan_create does, or for small layers a schedule of
+ * 32-query blocks; fewer blocks leave compute units to other streams, more
+ * run in several waves.  The plan's workspace size depends on
  * it.  MSSA_ERR_INVALID_ARG for attention_blocks < 0; otherwise as
  * mssa_plan_create. */
 mssa_status mssa_plan_create_ex(const mssa_plan_desc* desc, int32_t attention_blocks, mssa_plan* out);
