@@ -35,6 +35,7 @@
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
+#include "split_merge.hpp"
 
 namespace mssa {
 namespace {
@@ -412,19 +413,23 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
       const float mt = kQS ? halfwave_max(mx) + m_c : halfwave_max(mx) * c;
       if (__any(mt > m_run + kRescaleLog2)) {
         const float m_new = fmaxf(m_run, mt);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         l_part *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[db] *= alpha;
       }
+      // A query all of whose scores so far are -inf has m_run = -inf and no
+      // shift: its P are exp2(-inf) = 0, and its next tile comes here too.
+      const bool none = m_run == -INFINITY;
+      const float m_s = none ? 0.f : m_run;
       if constexpr (kQS) {
-        lt = exps(std::true_type{}, m_c - m_run, 0.f);
+        lt = exps(std::true_type{}, m_c - m_s, 0.f);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) cneg[e] = -m_run;
-        lbias = 0.f;
+        for (int e = 0; e < 16; ++e) cneg[e] = -m_s;
+        lbias = none ? INFINITY : 0.f;
       } else {
-        lt = exps(std::false_type{}, -m_run, 0.f);
+        lt = exps(std::false_type{}, -m_s, 0.f);
       }
     }
     l_part += lt;
@@ -689,7 +694,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
     for (int i = 0; i < kMaxMerge; ++i) {
       if (!have[i]) continue;
       const float mn = fmaxf(m, mv[i]);
-      const float so = __builtin_amdgcn_exp2f(m - mn), sj = __builtin_amdgcn_exp2f(mv[i] - mn);
+      const float so = split_weight<__bf16>(m, l, mn), sj = split_weight<__bf16>(mv[i], lv[i], mn);
 #pragma unroll
       for (int v = 0; v < NV; ++v) acc[v] = acc[v] * so + sj * ov[i][v];
       l = l * so + sj * lv[i];

@@ -33,11 +33,13 @@ def _desc(T, scales, H, W, F=1, S=1, Hh=1, nh=1, d=128, **kw):
 
 
 class BwdRun:
-    """Plan, seeded inputs and output gradient, one training pass on cuda:0."""
+    """Plan, seeded inputs and output gradient, one training pass on cuda:0.
+    attention_blocks as for mssa_plan_create_ex; inputs: this run -> the stored
+    inputs, in the place of the seeded ones."""
 
-    def __init__(self, desc, dtype, seed, amp, gamp=1.0):
+    def __init__(self, desc, dtype, seed, amp, gamp=1.0, attention_blocks=0, inputs=None):
         self.desc, self.dtype = dict(desc), dtype
-        self.plan = mssa.mssa_plan_create(dict(desc, dtype=dtype))
+        self.plan = mssa.mssa_plan_create_ex(dict(desc, dtype=dtype), attention_blocks)
         self.info = self.plan.info()
         shapes = input_shapes(desc, self.info["n_q"], self.info["n_sink_tok"], self.info["n_hist_tok"])
         # desc["q_prescaled"]: queries drawn at amp * softmax_scale * log2(e);
@@ -46,6 +48,8 @@ class BwdRun:
         self.qf = q_prescale(desc) if desc.get("q_prescaled") else 1.0
         self.x = make_inputs(shapes, seed, amp, dtype,
                              q_amplitude=amp * self.qf if desc.get("q_prescaled") else None)
+        if inputs is not None:
+            self.x = inputs(self)
         self.go = make_grad_output(shapes["q_win"], seed + 7919, gamp, dtype)
         self.d = {k: to_device(v, dtype) for k, v in self.x.items()}
         self.d_out = to_device(self.go, dtype)
@@ -55,11 +59,16 @@ class BwdRun:
         self.out = torch.empty_like(self.d["q_win"])
         self.lse = torch.empty(desc["num_heads"] * self.info["n_q"], dtype=torch.float32, device="cuda")
 
-    def run(self):
+    def forward(self):
         d = self.d
         mssa.mssa_pool_kv(self.plan, d["k_hist"], d["v_hist"], d["k_win"], d["v_win"], self.ws)
         mssa.mssa_forward_lse(self.plan, d["q_win"], d["k_sink"], d["v_sink"], d["k_hist"], d["v_hist"],
                               d["k_win"], d["v_win"], self.ws, self.out, self.lse)
+        torch.cuda.synchronize()
+
+    def run(self):
+        d = self.d
+        self.forward()
         g = {k: (None if d[k] is None else torch.empty_like(d[k])) for k in NAMES}
         mssa.mssa_backward(self.plan, d["q_win"], d["k_sink"], d["v_sink"], d["k_hist"], d["v_hist"],
                            d["k_win"], d["v_win"], self.out, self.lse, self.d_out, self.ws,
