@@ -424,7 +424,7 @@ void dkdv_kernel(BwdArgs a) {
   constexpr int BQ = kBwdStage;                         // queries per stage
   constexpr int QT = BQ * 256;                          // bytes of one swizzled tile (256-byte rows)
   constexpr int STB = 2 * QT;                           // Q | dO
-  constexpr int kStat = 1024;                           // -lse / scale | -rowsum | unused (256 bytes each, 128 used)
+  constexpr int kStat = 1024;                           // -lse / scale | unused | -rowsum | unused (256 bytes each, 128 used)
   constexpr int NBUF = 4;
   constexpr int NDMA = 2 * QT / 1024 / 4;               // 1 KB transfers per wave and stage
   constexpr int kStat0 = NBUF * STB, kV0 = kStat0 + NBUF * kStat;  // the stages' statistics, the block's V rows
@@ -469,7 +469,7 @@ void dkdv_kernel(BwdArgs a) {
 
   // This wave's transfers of a stage: 1 KB (4 rows) each, rows 4 (4 (wave & 1)
   // + i) + lane / 16 of the Q (waves 0, 1) or dO (waves 2, 3) tile, and a row
-  // statistic (waves 0, 1; lanes past the 32 queries read zeros).  Rows past
+  // statistic (waves 0, 2; lanes past the 32 queries read zeros).  Rows past
   // the range's end arrive as zeros with zero statistics: their P = 1 meets
   // zero dO rows and dS = 1 (0 - 0) = 0.
   const uint32_t row_bytes = static_cast<uint32_t>(ld) * 2;
@@ -483,15 +483,19 @@ void dkdv_kernel(BwdArgs a) {
   const __bf16* const x_head =
       static_cast<const __bf16*>(wave < 2 ? a.q : a.d_out) + hoff + static_cast<int64_t>(q_begin) * ld;
   const float* const s_head = (wave == 0 ? a.lse2 : a.dsum) + static_cast<int64_t>(head) * a.n_q + q_begin;
-  auto issue = [&](int t, int i) {  // transfer i of stage t (i == NDMA: the statistic); past the last stage zeros
-    const int nv = max(0, min(BQ, nq - t * BQ));
+  // Past the last stage waves 0 and 1 bring its Q and -lse / scale again (a
+  // finite P whatever K holds: a row of zeros would be NaN against an infinite
+  // key), waves 2 and 3 zeros for dO and -rowsum.
+  const int last = wave < 2 ? nst - 1 : 0x7fffffff;
+  auto issue = [&](int t, int i) {  // transfer i of stage t (i == NDMA: the statistic)
+    const int ts = min(t, last), nv = max(0, min(BQ, nq - ts * BQ));
     const uint32_t base = lds0 + (t & (NBUF - 1)) * STB;
     if (i < NDMA) {
-      const i32x4 rs = rsrc_of(x_head + static_cast<int64_t>(t) * BQ * ld, nv > 0 ? static_cast<uint32_t>(nv - 1) * row_bytes + D * 2 : 0u);
+      const i32x4 rs = rsrc_of(x_head + static_cast<int64_t>(ts) * BQ * ld, nv > 0 ? static_cast<uint32_t>(nv - 1) * row_bytes + D * 2 : 0u);
       dma16(rs, (voff0 ^ (i * 16)) + i * 4 * row_bytes, __builtin_amdgcn_readfirstlane(base + (wave * NDMA + i) * 1024));
     } else {
-      // waves 2 and 3 fill the unused part: every wave counts the same transfers
-      dma4(rsrc_of(s_head + t * BQ, static_cast<uint32_t>(nv) * 4), 4 * lane,
+      // waves 1 and 3 fill unused parts: every wave counts the same transfers
+      dma4(rsrc_of(s_head + ts * BQ, static_cast<uint32_t>(nv) * 4), 4 * lane,
            __builtin_amdgcn_readfirstlane(lds0 + kStat0 + (t & (NBUF - 1)) * kStat + wave * 256));
     }
   };
@@ -652,7 +656,7 @@ void dkdv_kernel(BwdArgs a) {
           if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][0] = v_op(i + 2 - 2 * N, 0);
         } else {
           if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][1] = v_op(i + 2 - 2 * N, 1);
-          if (ph == 1 && j == N - 2) load_stat(cur, 1);
+          if (ph == 1 && j == N - 2) load_stat(cur, 2);
           if (ph == 3 && j == N - 2) load_stat(next, 0);
         }
         if constexpr (ph == 0) {
@@ -689,7 +693,7 @@ void dkdv_kernel(BwdArgs a) {
   load_stat(0, 0);
 #pragma unroll
   for (int i = 0; i < kLead; ++i) ring[i] = operand(I0{}, i);
-  // Stages past the last one, which fill the round, are all zeros (a way out
+  // Stages past the last one, which fill the round, add nothing (a way out
   // between the steps made the compiler move the accumulators about).
   int t = 0;
   do {  // a group has queries
