@@ -428,9 +428,10 @@ void dkdv_kernel(BwdArgs a) {
   constexpr int NBUF = 4;
   constexpr int NDMA = 2 * QT / 1024 / 4;               // 1 KB transfers per wave and stage
   constexpr int kStat0 = NBUF * STB, kV0 = kStat0 + NBUF * kStat;  // the stages' statistics, the block's V rows
+  constexpr int kDump = kV0 + kBwdK * 256;              // 1 KB that nothing reads
   constexpr int kLead = 4;                              // chunks an operand is read ahead
   static_assert(BQ == 32 && NDMA == 4 && kBwdK == 256 && 4 * N % kLead == 0, "stage shape");
-  __shared__ __attribute__((aligned(16))) char lds[kV0 + kBwdK * 256];
+  __shared__ __attribute__((aligned(16))) char lds[kDump + 1024];
 
   const int b = blockIdx.x;
   int g = 0;
@@ -483,20 +484,23 @@ void dkdv_kernel(BwdArgs a) {
   const __bf16* const x_head =
       static_cast<const __bf16*>(wave < 2 ? a.q : a.d_out) + hoff + static_cast<int64_t>(q_begin) * ld;
   const float* const s_head = (wave == 0 ? a.lse2 : a.dsum) + static_cast<int64_t>(head) * a.n_q + q_begin;
-  // Past the last stage waves 0 and 1 bring its Q and -lse / scale again (a
-  // finite P whatever K holds: a row of zeros would be NaN against an infinite
-  // key), waves 2 and 3 zeros for dO and -rowsum.
-  const int last = wave < 2 ? nst - 1 : 0x7fffffff;
-  auto issue = [&](int t, int i) {  // transfer i of stage t (i == NDMA: the statistic)
-    const int ts = min(t, last), nv = max(0, min(BQ, nq - ts * BQ));
-    const uint32_t base = lds0 + (t & (NBUF - 1)) * STB;
+  // Past the last stage dO and -rowsum are zeros, and the queries and their
+  // -lse / scale stay those of the buffer's previous stage (the transfers'
+  // zeros go to kDump): a finite P whatever K holds, where a row of zeros
+  // would be NaN against an infinite key.  Bringing the last stage again
+  // instead cost its time: 2 of 38 us where 25 stages fill 28.
+  auto issue = [&](int ts, int t, int i) {  // transfer i of stage ts into buffer t % 4 (i == NDMA: the statistic)
+    const int nv = max(0, min(BQ, nq - ts * BQ));
+    const bool keep = wave < 2 && nv == 0;
     if (i < NDMA) {
       const i32x4 rs = rsrc_of(x_head + static_cast<int64_t>(ts) * BQ * ld, nv > 0 ? static_cast<uint32_t>(nv - 1) * row_bytes + D * 2 : 0u);
-      dma16(rs, (voff0 ^ (i * 16)) + i * 4 * row_bytes, __builtin_amdgcn_readfirstlane(base + (wave * NDMA + i) * 1024));
+      const uint32_t dst = (t & (NBUF - 1)) * STB + (wave * NDMA + i) * 1024;
+      dma16(rs, (voff0 ^ (i * 16)) + i * 4 * row_bytes, __builtin_amdgcn_readfirstlane(lds0 + (keep ? kDump : dst)));
     } else {
       // waves 1 and 3 fill unused parts: every wave counts the same transfers
+      const uint32_t dst = kStat0 + (t & (NBUF - 1)) * kStat + wave * 256;
       dma4(rsrc_of(s_head + ts * BQ, static_cast<uint32_t>(nv) * 4), 4 * lane,
-           __builtin_amdgcn_readfirstlane(lds0 + kStat0 + (t & (NBUF - 1)) * kStat + wave * 256));
+           __builtin_amdgcn_readfirstlane(lds0 + (keep ? kDump : dst)));
     }
   };
 
@@ -506,7 +510,12 @@ void dkdv_kernel(BwdArgs a) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int i = 0; i <= NDMA; ++i) issue(t, i);
+    for (int i = 0; i <= NDMA; ++i) issue(t, t, i);
+  // fewer stages than buffers: the others hold the last stage's queries
+  if (wave < 2)
+    for (int t = nst; t < NBUF; ++t)
+#pragma unroll
+      for (int i = 0; i <= NDMA; ++i) issue(nst - 1, t, i);
   bf16x8 kf[2][N];
   {
     constexpr int CH = D / 8, RP = kBwdKVThreads / CH, NV = kBwdK / RP;  // 16-byte chunks per row, rows per pass, passes
@@ -523,8 +532,8 @@ void dkdv_kernel(BwdArgs a) {
       for (int ks = 0; ks < N; ++ks)
         kf[kb][ks] = kp ? *reinterpret_cast<const bf16x8*>(kp + hoff + hh * 8 + ks * 16) : bf16x8{};
     }
-    // the buffer of stage -1 (multiplied by dS = 0 in the first step)
-    for (int i = tid; i < QT / 16; i += kBwdKVThreads)
+    // the queries of stage -1 (multiplied by dS = 0 in the first step)
+    for (int i = nst < NBUF ? QT / 16 : tid; i < QT / 16; i += kBwdKVThreads)
       reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB)[i] = bf16x8{};
 #pragma unroll
     for (int i = 0; i < NV; ++i)
@@ -660,7 +669,7 @@ void dkdv_kernel(BwdArgs a) {
           if (ph == 3 && j == N - 2) load_stat(next, 0);
         }
         if constexpr (ph == 0) {
-          if (sl <= NDMA) issue(t + 2, sl);  // before the stores: the wait above counts on it
+          if (sl <= NDMA) issue(t + 2, t + 2, sl);  // before the stores: the wait above counts on it
           if (N == 4 && sl == 2 * N - 2) {
             ds_store(t - 1, 0, 0);
             ds_store(t - 1, 0, 1);
