@@ -739,8 +739,6 @@ mssa_status mssa_backward(mssa_plan plan, const void* q_win, const void* k_sink,
     a.n_groups = G;
     set_score_scales(p, a.scale, a.scale_log2e);
     a.q_prescaled = p.q_prescaled ? 1 : 0;
-    a.dq_splits = p.dq_splits;
-    a.dq_partial = p.dq_splits > 1 ? reinterpret_cast<float*>(ws + p.partial_off) : nullptr;
     const int qb = bf16 ? mssa::kBwdQ : mssa::kBwdF32, kb = bf16 ? mssa::kBwdK : mssa::kBwdF32;
     const KvSources src{k_sink, v_sink, k_hist, v_hist, nullptr, nullptr, k_win, v_win, ws};
     int gi = 0;
@@ -762,6 +760,7 @@ mssa_status mssa_backward(mssa_plan plan, const void* q_win, const void* k_sink,
       A.ds = bf16 ? ws + p.bwd_ds_off[g] : nullptr;
       A.ds_stages = p.bwd_ds_stages[g];
       A.ds_qblocks = p.bwd_ds_qblocks[g];
+      A.dq_splits = p.bwd_dq_splits[g];
       A.n_qblocks = (Q.q_end - Q.q_begin + qb - 1) / qb;
       A.n_kblocks = static_cast<int32_t>((Q.n_kv + kb - 1) / kb);
     }

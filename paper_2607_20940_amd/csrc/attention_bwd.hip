@@ -141,7 +141,9 @@ __device__ inline int swz(int row, int col) { return swz256(row, col); }
 // them.  A block's chain of stages is bound by their latency (about 0.85 us
 // each), so where the blocks leave CUs idle the context is split over
 // dq_splits of them (6 heads of 64 on 17 x 23: 36 blocks, 45 us; with 7 splits
-// 10 us and 5 us for the sum).
+// 15 us and 5 us for the sum).  A split's sum (fp32) takes the place of the dS
+// tiles its wave has read, which no one else reads: D / 32 tiles' bytes, so a
+// split has at least as many stages (dq_splits of its group, 1: no split).
 template <int D>
 __global__ __launch_bounds__(kBwdQThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void dq_kernel(BwdArgs a) {
@@ -160,11 +162,12 @@ void dq_kernel(BwdArgs a) {
   static_assert(NK * 1024 * NW == KT && NW * 32 == kBwdQ && BN % 32 == 0 && NDS % 2 == 0, "stage shape");
   __shared__ __attribute__((aligned(16))) char lds[3 * STB];
 
-  // dq_splits > 1: block b takes context split b / dq_blocks
+  // block b takes context split b / dq_blocks, if its group has that many
   const int sp = blockIdx.x / a.dq_blocks, b = blockIdx.x - sp * a.dq_blocks;
   int g = 0;
   while (g + 1 < a.n_groups && b >= a.groups[g + 1].dq_block_begin) ++g;
   const BwdGroupArgs& G = a.groups[g];
+  if (sp >= G.dq_splits) return;
   const int idx = xcd_remap(b - G.dq_block_begin, G.n_qblocks * a.num_heads);
   const int hl = idx / G.n_qblocks, qt = idx % G.n_qblocks;  // head of the launch
   const int head = a.head0 + hl;
@@ -184,8 +187,8 @@ void dq_kernel(BwdArgs a) {
   const int nr = G.n_runs;
   int nst = 0;
   for (int r = 0; r < nr; ++r) nst += (G.runs[r].n_tok + BN - 1) / BN;
-  const int st0 = static_cast<int>(static_cast<int64_t>(nst) * sp / a.dq_splits);  // this split's first stage
-  nst = static_cast<int>(static_cast<int64_t>(nst) * (sp + 1) / a.dq_splits) - st0;
+  const int st0 = static_cast<int>(static_cast<int64_t>(nst) * sp / G.dq_splits);  // this split's first stage
+  nst = static_cast<int>(static_cast<int64_t>(nst) * (sp + 1) / G.dq_splits) - st0;
   struct Stream {
     const __bf16* k;
     int left;  // tokens of the current run from k on
@@ -220,7 +223,7 @@ void dq_kernel(BwdArgs a) {
     const int lc = unswz256(row, phys);
     voff[i] = lc < D / 8 ? row * row_bytes + lc * 16 : kPastEnd;
   }
-  const __bf16* const ds_wave = static_cast<const __bf16*>(G.ds) +
+  __bf16* const ds_wave = static_cast<__bf16*>(G.ds) +
       ((static_cast<int64_t>(hl) * G.ds_qblocks + (wave_ok ? qb : 0)) * G.ds_stages + st0) * (BN * 32);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   auto issue = [&](const Stream& s, int st, int buf) {
@@ -312,10 +315,11 @@ void dq_kernel(BwdArgs a) {
     __syncthreads();
   }
 
-  if (a.dq_splits > 1) {
-    // this split's sum, in fp32 where dq_sum_kernel finds it
-    if (wave_ok && q_row < G.q_end) {
-      float* op = a.dq_partial + (static_cast<int64_t>(sp) * a.n_q + q_row) * ld + hoff + 4 * hh;
+  if (G.dq_splits > 1) {
+    // this split's sum where dq_sum_kernel finds it; the last stage's wait and
+    // barrier have passed, so the wave's tiles are read
+    if (wave_ok) {
+      f32x4* op = reinterpret_cast<f32x4*>(ds_wave) + lane;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -323,7 +327,7 @@ void dq_kernel(BwdArgs a) {
           f32x4 v;
 #pragma unroll
           for (int i = 0; i < 4; ++i) v[i] = acc[db][4 * jj + i];
-          *reinterpret_cast<f32x4*>(op + db * 32 + 8 * jj) = v;
+          op[(db * 4 + jj) * 64] = v;
         }
     }
     return;
@@ -342,17 +346,56 @@ void dq_kernel(BwdArgs a) {
   }
 }
 
-// dQ from the fp32 sums of the context splits, split 0 first.
-__global__ __launch_bounds__(kDotThreads) void dq_sum_kernel(BwdArgs a) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kDotThreads + threadIdx.x, n = a.n_q * a.ld / 4;
-  if (i >= n) return;
-  const f32x4* p = reinterpret_cast<const f32x4*>(a.dq_partial) + i;
-  f32x4 s = p[0];
-  for (int k = 1; k < a.dq_splits; ++k) s += p[k * n];
-  bf16x4 v;
+// dQ from the fp32 sums of the context splits, split 0 first.  A block per
+// 32-query block and head, a wave per 32 channels, lanes as in dq_kernel.
+template <int D>
+__global__ __launch_bounds__(2 * D) void dq_sum_kernel(BwdArgs a) {
+  static_assert(2 * D == 64 * Lay<D>::DB, "a wave per 32 channels");
+  int g = 0, b = blockIdx.x;
+  for (; g + 1 < a.n_groups; ++g) {
+    const int n = a.groups[g].dq_splits > 1 ? (a.groups[g].q_end - a.groups[g].q_begin + 31) / 32 * a.num_heads : 0;
+    if (b < n) break;
+    b -= n;
+  }
+  const BwdGroupArgs& G = a.groups[g];
+  const int nqb = (G.q_end - G.q_begin + 31) / 32, hl = b / nqb, qb = b % nqb;
+  const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5, db = threadIdx.x >> 6;
+  const __bf16* tiles = static_cast<const __bf16*>(G.ds) +
+                        (static_cast<int64_t>(hl) * G.ds_qblocks + qb) * G.ds_stages * (kBwdKS * 32);
+  f32x4 s[4] = {};
+  auto add = [&](auto n_c, int k0) {  // splits k0 .. k0 + n - 1, their loads in flight together
+    constexpr int N = decltype(n_c)::value;
+    f32x4 v[N][4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] = static_cast<__bf16>(s[j] * a.scale);
-  reinterpret_cast<bf16x4*>(a.dq)[i] = v;
+    for (int k = 0; k < N; ++k) {
+      const int64_t st0 = static_cast<int64_t>(G.ds_stages) * (k0 + k) / G.dq_splits;
+      const f32x4* p = reinterpret_cast<const f32x4*>(tiles + st0 * (kBwdKS * 32)) + db * 256 + lane;
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) v[k][jj] = p[jj * 64];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) s[jj] += v[k][jj];
+  };
+  int k = 0;
+  for (; k + 4 <= G.dq_splits; k += 4) add(std::integral_constant<int, 4>{}, k);
+  if (k + 2 <= G.dq_splits) {
+    add(std::integral_constant<int, 2>{}, k);
+    k += 2;
+  }
+  if (k < G.dq_splits) add(std::integral_constant<int, 1>{}, k);
+  const int q_row = G.q_begin + qb * 32 + 8 * ((n & 15) >> 2) + 4 * (n >> 4) + (n & 3);
+  if (q_row >= G.q_end) return;
+  __bf16* op = static_cast<__bf16*>(a.dq) + static_cast<int64_t>(q_row) * a.ld +
+               static_cast<int64_t>(a.head0 + hl) * D + 4 * hh + db * 32;
+#pragma unroll
+  for (int jj = 0; jj < 4; ++jj) {
+    bf16x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = static_cast<__bf16>(s[jj][i] * a.scale);
+    *reinterpret_cast<bf16x4*>(op + 8 * jj) = v;
+  }
 }
 
 // ------------------------------------------------------------------ bf16: dK, dV
@@ -838,16 +881,27 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
   if (dq_blocks > 0) {
     BwdArgs d = a;
     d.dq_blocks = dq_blocks;
-    const int64_t grid = static_cast<int64_t>(dq_blocks) * d.dq_splits;
-    if (d.dq_splits < 1 || grid > 0x7fffffff || (d.dq_splits > 1 && !d.dq_partial)) return hipErrorInvalidValue;
+    int splits = 1;
+    int64_t sums = 0;
+    for (int g = 0; g < d.n_groups; ++g) {
+      const BwdGroupArgs& G = d.groups[g];
+      // a split's sum lies in the dS tiles of its stages
+      if (G.dq_splits < 1 || (G.dq_splits > 1 && G.ds_stages / G.dq_splits < head_dim / 32)) return hipErrorInvalidValue;
+      splits = G.dq_splits > splits ? G.dq_splits : splits;
+      if (G.dq_splits > 1) sums += static_cast<int64_t>((G.q_end - G.q_begin + 31) / 32) * d.num_heads;
+    }
+    const int64_t grid = static_cast<int64_t>(dq_blocks) * splits;
+    if (grid > 0x7fffffff || sums > 0x7fffffff) return hipErrorInvalidValue;
     if (head_dim == 128)
       hipLaunchKernelGGL(dq_kernel<128>, dim3(static_cast<uint32_t>(grid)), dim3(kBwdQThreads), 0, stream, d);
     else
       hipLaunchKernelGGL(dq_kernel<64>, dim3(static_cast<uint32_t>(grid)), dim3(kBwdQThreads), 0, stream, d);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || d.dq_splits == 1) return e;
-    const int64_t n = (d.n_q * d.ld / 4 + kDotThreads - 1) / kDotThreads;
-    hipLaunchKernelGGL(dq_sum_kernel, dim3(static_cast<uint32_t>(n)), dim3(kDotThreads), 0, stream, d);
+    if (e != hipSuccess || sums == 0) return e;
+    if (head_dim == 128)
+      hipLaunchKernelGGL(dq_sum_kernel<128>, dim3(static_cast<uint32_t>(sums)), dim3(256), 0, stream, d);
+    else
+      hipLaunchKernelGGL(dq_sum_kernel<64>, dim3(static_cast<uint32_t>(sums)), dim3(128), 0, stream, d);
     return hipGetLastError();
   }
   return hipSuccess;

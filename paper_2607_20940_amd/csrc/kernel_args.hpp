@@ -104,6 +104,8 @@ struct BwdGroupArgs {
   void* ds;                   // bf16: dS tiles [launch heads][ds_qblocks][ds_stages][64 keys][32 queries]
   int32_t ds_stages;          // 64-key stages of the runs (each run starts a stage)
   int32_t ds_qblocks;         // 32-query blocks (even)
+  int32_t dq_splits;          // bf16 dQ kernel: blocks that share the context of 256 queries
+  int32_t pad;
 };
 
 struct BwdArgs {
@@ -121,9 +123,7 @@ struct BwdArgs {
   float scale;              // softmax scale
   float scale_log2e;
   int32_t q_prescaled;      // queries arrive multiplied by scale * log2(e)
-  int32_t dq_splits;        // bf16 dQ kernel: blocks that share the context of 256 queries
-  int32_t dq_blocks;        // its blocks per split (set by the launcher)
-  float* dq_partial;        // dq_splits > 1: fp32 sums [dq_splits][n_q][ld]
+  int32_t dq_blocks;        // bf16 dQ kernel: blocks per split (set by the launcher)
   BwdGroupArgs groups[kMaxGroups];  // longest query range first
 };
 static_assert(sizeof(BwdArgs) <= 4096, "kernel argument block");

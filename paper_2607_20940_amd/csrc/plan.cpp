@@ -333,23 +333,43 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     if (p.n_ranges > 1) p.range_table_off = ws + p.partial_bytes - align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
   }
   p.sched = make_schedule(p, run_tok);
-  if (d.dtype == MSSA_BF16) {
-    // dQ of a layer with few 256-query blocks: splits of at least six 64-key
-    // stages of the longest context.  Their sums may take the place of the
-    // forward's records.
-    int64_t stages = 0;
-    for (int64_t n : run_tok[p.order.front()]) stages += (n + kBwdKS - 1) / kBwdKS;
-    const int64_t s = std::max<int64_t>(1, std::min({slots / n_items, stages / 6, int64_t{8}}));
-    const int64_t bytes = s > 1 ? align256(s * p.n_q * p.ld * 4) : 0;
-    if (s > 1 && !p.hist_ring && (room < 0 || std::max(p.partial_bytes, bytes) <= room)) {
-      p.dq_splits = static_cast<int32_t>(s);
-      p.partial_bytes = std::max(p.partial_bytes, bytes);
-    }
-  }
   ws += p.partial_bytes;
   p.workspace_bytes = ws;
 
   // Backward workspace and the scatter of context gradients to the sources.
+  // dS of whole heads per launch within the budget, at least one head.
+  p.bwd_ds_stages.assign(G, 0);
+  p.bwd_ds_qblocks.assign(G, 0);
+  p.bwd_dq_splits.assign(G, 1);
+  p.bwd_ds_heads = d.num_heads;
+  if (d.dtype == MSSA_BF16) {
+    int64_t per_head = 0, longest = 0;
+    for (int g = 0; g < G; ++g) {
+      int64_t stages = 0;
+      for (const Run& r : p.runs[g]) stages += (r.n_tok + kBwdKS - 1) / kBwdKS;
+      const int64_t nq = p.groups[g].q_end - p.groups[g].q_begin;
+      const int64_t qblocks = 2 * ((nq + kBwdQS - 1) / kBwdQS);
+      // the dK/dV kernel addresses a stage's two 32-query blocks of tiles
+      // with 32-bit offsets
+      if (stages * 2 * kBwdKS * 64 > 0xffffffffLL || qblocks > 0x7fffffff) {
+        err = "backward dS buffer too large";
+        return MSSA_ERR_UNSUPPORTED;
+      }
+      p.bwd_ds_stages[g] = static_cast<int32_t>(stages);
+      p.bwd_ds_qblocks[g] = static_cast<int32_t>(qblocks);
+      per_head += qblocks * stages * kBwdKS * 32 * 2;
+      longest = std::max(longest, stages);
+    }
+    p.bwd_ds_heads = static_cast<int32_t>(
+        std::max<int64_t>(1, std::min<int64_t>(d.num_heads, kBwdDsBudget / std::max<int64_t>(1, per_head))));
+    // dQ of a layer with few 256-query blocks: splits of at least six 64-key
+    // stages of the longest context, and of enough stages of the group's own
+    // for a split's sum to lie in their dS tiles.
+    const int64_t splits = std::max<int64_t>(1, std::min({slots / n_items, longest / 6, int64_t{8}}));
+    for (int g = 0; g < G; ++g)
+      p.bwd_dq_splits[g] = static_cast<int32_t>(
+          std::max<int64_t>(1, std::min<int64_t>(splits, p.bwd_ds_stages[g] / (d.head_dim / 32))));
+  }
   ws = align256(ws);
   p.bwd_dsum_off = ws;
   ws += align256(static_cast<int64_t>(d.num_heads) * p.n_q * 4);
@@ -365,35 +385,11 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     ws += bytes;
   }
   p.bwd_ds_off.assign(G, 0);
-  p.bwd_ds_stages.assign(G, 0);
-  p.bwd_ds_qblocks.assign(G, 0);
-  p.bwd_ds_heads = d.num_heads;
-  if (d.dtype == MSSA_BF16) {
-    int64_t per_head = 0;
-    for (int g = 0; g < G; ++g) {
-      int64_t stages = 0;
-      for (const Run& r : p.runs[g]) stages += (r.n_tok + kBwdKS - 1) / kBwdKS;
-      const int64_t nq = p.groups[g].q_end - p.groups[g].q_begin;
-      const int64_t qblocks = 2 * ((nq + kBwdQS - 1) / kBwdQS);
-      // the dK/dV kernel addresses a stage's two 32-query blocks of tiles
-      // with 32-bit offsets
-      if (stages * 2 * kBwdKS * 64 > 0xffffffffLL || qblocks > 0x7fffffff) {
-        err = "backward dS buffer too large";
-        return MSSA_ERR_UNSUPPORTED;
-      }
-      p.bwd_ds_stages[g] = static_cast<int32_t>(stages);
-      p.bwd_ds_qblocks[g] = static_cast<int32_t>(qblocks);
-      per_head += qblocks * stages * kBwdKS * 32 * 2;
-    }
-    // whole heads per chunk within the budget, at least one
-    p.bwd_ds_heads = static_cast<int32_t>(
-        std::max<int64_t>(1, std::min<int64_t>(d.num_heads, kBwdDsBudget / std::max<int64_t>(1, per_head))));
-    if (p.bwd_ds_heads < d.num_heads) p.dq_splits = 1;  // the splits' sums are added up once, for all heads
+  if (d.dtype == MSSA_BF16)
     for (int g = 0; g < G; ++g) {
       p.bwd_ds_off[g] = ws;
       ws += align256(static_cast<int64_t>(p.bwd_ds_heads) * p.bwd_ds_qblocks[g] * p.bwd_ds_stages[g] * kBwdKS * 32 * 2);
     }
-  }
   p.bwd_workspace_bytes = ws;
   auto seg_of = [&](int g, int32_t kind, int32_t frame) -> const SegRow& {
     for (const SegRow& r : p.segs)

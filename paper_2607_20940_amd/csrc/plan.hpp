@@ -131,8 +131,7 @@ struct Plan {
   std::vector<int64_t> bwd_ds_off;      // bytes, per group
   std::vector<int32_t> bwd_ds_stages;   // 64-key stages of the group's runs
   std::vector<int32_t> bwd_ds_qblocks;  // 32-query blocks, rounded up to an even count
-  int32_t dq_splits = 1;    // bf16 backward: blocks that share the context of 256 queries in the dQ kernel; their
-                            // sums take the place of the forward's partial records
+  std::vector<int32_t> bwd_dq_splits;   // blocks that share the context of 256 queries in the bf16 dQ kernel
   int64_t bwd_workspace_bytes;
   std::vector<ScatterJob> scatter_jobs;
 };

@@ -235,6 +235,10 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
           int64_t{G.n_qblocks} * kBwdQ > int64_t{G.ds_qblocks} * 32 + kBwdQ - 32)
         failure("backward: dS query blocks");
       check_range(G.ds, int64_t{a.num_heads} * G.ds_qblocks * G.ds_stages * kBwdKS * 32 * 2, "backward dS tiles");
+      // a dQ split's sum (32 queries, fp32) lies in the dS tiles of its stages
+      if (G.dq_splits < 1 ||
+          (G.dq_splits > 1 && G.ds_stages / G.dq_splits * kBwdKS * 32 * 2 < int64_t{32} * head_dim * 4))
+        failure("backward: dQ splits");
     }
   }
   if (qblocks != dq_blocks || kblocks != kv_blocks) failure("backward: grid size");

@@ -1,6 +1,7 @@
 """Workspace of plans that choose between schedules (no GPU needed): the
 records a schedule needs never push a plan past the scratch of the entry point
-without allocations when another schedule fits."""
+without allocations when another schedule fits, and the forward's workspace
+holds nothing but the pooled blocks and those records."""
 
 import pytest
 
@@ -39,3 +40,17 @@ def test_given_attention_blocks_are_kept():
         base = _plan(4, "bf16", 1, grid=32, flags=mssa.MSSA_PLAN_POOLED_HIST_RING).info()["workspace_bytes"]
         ws = _plan(4, "bf16", blocks, grid=32, flags=mssa.MSSA_PLAN_POOLED_HIST_RING).info()["workspace_bytes"]
         assert ws == base + blocks * rec + ((blocks + 1) * 8 + 255) // 256 * 256
+
+
+def _align(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("scales, heads, d, hist", [([1], 1, 128, 20), ([1, 2], 2, 64, 30), ([1, 1, 2, 4], 3, 128, 9)])
+def test_forward_workspace_holds_nothing_of_the_backward(scales, heads, d, hist):
+    """One range and no records: the pooled blocks alone, also where the
+    backward splits dQ (few query items on a long context)."""
+    desc = dict(num_states=len(scales), scales=scales, grid_h=16, grid_w=16, frames_per_state=1, sink_frames=1,
+                hist_frames=hist, num_heads=heads, head_dim=d, dtype="bf16")
+    info = mssa.mssa_plan_create_ex(desc, 1).info()
+    assert info["workspace_bytes"] == 2 * sum(_align(n * heads * d * 2) for n in info["pooled_tokens"])
