@@ -35,7 +35,6 @@
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
-#include "split_merge.hpp"
 
 namespace mssa {
 namespace {
@@ -55,6 +54,12 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 constexpr float kRescaleLog2 = 8.0f;
 constexpr float kRescaleSum = 256.0f;  // 2^kRescaleLog2
 constexpr float kLn2 = 0.6931471805599453f;
+
+// Running max of a query that has seen no score above -inf: finite, so that
+// its P are exp2(-inf) = 0 and its piece weighs nothing in the merge (with -inf
+// both would be NaN), and below every finite score, so that the first of them
+// takes the max path.
+constexpr float kNoMax = -__FLT_MAX__;
 
 // ---------------------------------------------------------------------------
 // Persistent schedule.  An item is one (query scale, head, 256-query tile); its
@@ -192,13 +197,13 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
   f32x16 o[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) o[db] = f32x16{};
-  float m_run = -INFINITY;  // running max in the exp2 domain (shared by both half-waves)
+  float m_run = kNoMax;     // running max in the exp2 domain (shared by both half-waves)
   float l_part = 0.f;       // this lane's share of the row sum
   // kQS only.  Accumulator input of the first MFMA of every S chain: -m_c in
   // all 16 elements (a lane's 16 elements all belong to its query), with
-  // m_c = m_run once the first tile has set it and 0 before, so S arrives as
-  // S - m_c.  The first tile's row sum is seeded with +inf (lbias), which
-  // sends that tile through the max path whatever the size of its scores.
+  // m_c = m_run once a tile has set it and 0 before, so S arrives as S - m_c.
+  // Up to that tile the row sum is seeded with +inf (lbias), which sends it
+  // through the max path whatever the size of its scores.
   f32x16 cneg = f32x16{};
   float lbias = INFINITY;
   f32x16 s[BN / 32];
@@ -364,7 +369,7 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
   // operand of the next P V, with m the running max.  Lazy rescaling without
   // a per-tile max: P is first computed against the current m; if every
   // lane's sum over its 32 keys stays <= 2^kRescaleLog2, so does every P and
-  // nothing else is needed.  Otherwise (the first tile, where m is -inf, or
+  // nothing else is needed.  Otherwise (the first tile, where m is kNoMax, or
   // scores well above m) the tile max is taken, m is raised if the max
   // exceeds it by more than kRescaleLog2 (O and l scaled down), and P is
   // recomputed (kQS: the new -m also goes into the accumulator input of the
@@ -413,23 +418,20 @@ __device__ __forceinline__ void attend_piece(const FwdArgs& a, const FwdGroupArg
       const float mt = kQS ? halfwave_max(mx) + m_c : halfwave_max(mx) * c;
       if (__any(mt > m_run + kRescaleLog2)) {
         const float m_new = fmaxf(m_run, mt);
-        const float alpha = m_new == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         l_part *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[db] *= alpha;
       }
-      // A query all of whose scores so far are -inf has m_run = -inf and no
-      // shift: its P are exp2(-inf) = 0, and its next tile comes here too.
-      const bool none = m_run == -INFINITY;
-      const float m_s = none ? 0.f : m_run;
       if constexpr (kQS) {
-        lt = exps(std::true_type{}, m_c - m_s, 0.f);
+        const float ms = m_run == kNoMax ? 0.f : m_run;  // what the next MFMA subtracts
+        lt = exps(std::true_type{}, m_c - m_run, 0.f);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) cneg[e] = -m_s;
-        lbias = none ? INFINITY : 0.f;
+        for (int e = 0; e < 16; ++e) cneg[e] = -ms;
+        lbias = m_run == kNoMax ? INFINITY : 0.f;
       } else {
-        lt = exps(std::false_type{}, -m_s, 0.f);
+        lt = exps(std::false_type{}, -m_run, 0.f);
       }
     }
     l_part += lt;
@@ -694,7 +696,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(FwdArgs a) {
     for (int i = 0; i < kMaxMerge; ++i) {
       if (!have[i]) continue;
       const float mn = fmaxf(m, mv[i]);
-      const float so = split_weight<__bf16>(m, l, mn), sj = split_weight<__bf16>(mv[i], lv[i], mn);
+      const float so = __builtin_amdgcn_exp2f(m - mn), sj = __builtin_amdgcn_exp2f(mv[i] - mn);
 #pragma unroll
       for (int v = 0; v < NV; ++v) acc[v] = acc[v] * so + sj * ov[i][v];
       l = l * so + sj * lv[i];

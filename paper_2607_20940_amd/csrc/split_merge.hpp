@@ -1,11 +1,10 @@
-// Merge of attention pieces: the weight of a piece (all forward kernels), and
-// the merge of the kernels whose eight waves split the context of one 32-query
-// item (attention_f32.hip, attention_fwd_small.hip).  There each wave ends with
-// an unnormalised output O (fp32), the running max m and the row sum l of the
-// keys it saw; the waves meet in LDS, and when the context is also split over
-// blocks (FwdArgs::key_splits > 1) each block's sum is a record in the
-// workspace that combine_split_kernel merges.  Fixed orders (wave 0 first,
-// split 0 first): the same bits on every run.
+// Merge of attention pieces for the kernels whose eight waves split the
+// context of one 32-query item (attention_f32.hip, attention_fwd_small.hip).
+// Each wave ends with an unnormalised output O (fp32), the running max m and
+// the row sum l of the keys it saw; the waves meet in LDS, and when the
+// context is also split over blocks (FwdArgs::key_splits > 1) each block's
+// sum is a record in the workspace that combine_split_kernel merges.  Fixed
+// orders (wave 0 first, split 0 first): the same bits on every run.
 //
 // Layout of O in LDS and in a record: V consecutive channels of one query are
 // neighbours, the queries of one channel group next to each other: element
