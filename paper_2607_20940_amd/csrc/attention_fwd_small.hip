@@ -12,7 +12,7 @@
 // the merge.  K of the next tile is in flight during softmax and P V, V during
 // the scores; two waves share a SIMD and cover each other's waits.  The price
 // is K/V read once per 32 queries instead of once per 256, so the L2 bounds it
-// and the dispatch (small_layer_splits in plan.cpp) keeps it to small layers.
+// and the dispatch (forward_choice in plan.cpp) keeps it to small layers.
 // Measured, pass: 2 heads of 128 on a 10 x 13 grid 55.9 -> 18.3 us, 6 heads of
 // 64 on 17 x 23 79.8 -> 24.9 us (25.8 with the scale applied to every score
 // before the maximum and the mask on every tile).

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <limits>
+#include <map>
 
 namespace mssa {
 namespace {
@@ -21,42 +22,133 @@ bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
 
 int32_t ceil_div(int32_t a, int32_t b) { return (a + b - 1) / b; }
 
-// Blocks per 32-query item of fwd_small_kernel, or 0 for the persistent
-// 256-query kernel: the one expected to be faster, in nanoseconds fitted on an
-// MI355X over layers of 1 to 18 heads of 64 and 128 and 1e9 to 2e11 FLOP.
-// Small kernel: 6 us and, per step of eight 32-key tiles (one per wave), 1.25
-// us for the longest context, or 1.9 us for the average block where all CUs
-// stream K/V at once; merging S blocks per item adds 5 us and 1.5 us per
-// block.  Persistent kernel: 28 us (its pieces' fill, records and merge) and
-// 1e15 FLOP/s.  Measured, small / persistent: 2 heads of 128 on 10 x 13 18 /
-// 35 us, 6 heads of 64 on 17 x 23 28 / 39 us, 5 heads of 128 on 13 x 18 52 /
-// 51 us, 4 heads of 128 on 15 x 26 with 12 history frames 113 / 80 us.
-int32_t small_layer_splits(const Plan& p, const std::vector<std::vector<int64_t>>& run_tok, int64_t cus) {
-  int64_t longest = 0;
-  double items = 0, steps = 0, flops = 0;
-  for (size_t g = 0; g < p.groups.size(); ++g) {
-    int64_t tiles = 0;
-    for (int64_t n : run_tok[g]) tiles += (n + 31) / 32;
-    const double nq = p.groups[g].q_end - p.groups[g].q_begin;
-    const double it = std::ceil(nq / kFwdF32BM) * p.desc.num_heads;
-    const int64_t st = (tiles + kSplitWaves - 1) / kSplitWaves;
-    longest = std::max(longest, st);
-    items += it;
-    steps += it * st;
-    flops += 4.0 * p.desc.head_dim * p.desc.num_heads * nq * p.groups[g].n_kv;
+int64_t align256(int64_t x) { return (x + 255) / 256 * 256; }
+
+// Partial records and range table of n tile ranges of the persistent forward.
+int64_t range_records(const Plan& p, int64_t n) {
+  return n > 1 ? align256(2 * n * partial_record_floats(p.desc.head_dim) * 4) + align256((n + 1) * 8) : 0;
+}
+
+// 32-query items, and the records of s blocks for each of them.
+int64_t items_32q(const Plan& p) {
+  int64_t n = 0;
+  for (const QGroup& g : p.groups) n += int64_t{ceil_div(g.q_end - g.q_begin, kFwdF32BM)} * p.desc.num_heads;
+  return n;
+}
+int64_t split_records(const Plan& p, int64_t s) {
+  return s > 1 ? align256(items_32q(p) * s * split_record_floats(p.desc.head_dim) * 4) : 0;
+}
+
+// Blocks of one cost (microseconds), and the time of blocks dealt out in this
+// order over `cus` CUs, one at a time on each: an XCD's CUs share a contiguous
+// eighth of them (xcd_remap of the kernels).
+struct BlockRun {
+  int64_t n;
+  double cost;
+};
+double dealt_out(const std::vector<BlockRun>& runs, int64_t cus) {
+  constexpr int64_t kXcds = 8;
+  int64_t blocks = 0;
+  for (const BlockRun& r : runs) blocks += r.n;
+  double worst = 0;
+  for (int64_t x = 0; x < kXcds; ++x) {
+    const int64_t lo = blocks * x / kXcds, hi = blocks * (x + 1) / kXcds;
+    std::map<double, int64_t> busy{{0.0, std::max<int64_t>(1, cus / kXcds)}};  // CUs by the time they are free
+    int64_t first = 0;
+    for (const BlockRun& r : runs) {
+      int64_t left = std::min(hi, first + r.n) - std::max(lo, first);
+      first += r.n;
+      while (left > 0) {
+        const auto it = busy.begin();
+        const auto [t, free] = *it;
+        const int64_t k = std::min(left, free);
+        busy.erase(it);
+        if (free > k) busy[t] += free - k;
+        busy[t + r.cost] += k;
+        left -= k;
+      }
+    }
+    if (hi > lo) worst = std::max(worst, busy.rbegin()->first);
   }
-  double best = 28e3 + flops * 1e-6;
-  int32_t splits = 0;
-  for (int32_t s = 1; s <= 8 && s <= longest; s *= 2) {
-    if (s > 1 && items * s > cus) break;
-    const double t = 6e3 + (s > 1 ? 5e3 + 1.5e3 * s : 0.0) +
-                     std::max(1.25e3 * static_cast<double>((longest + s - 1) / s), 1.9e3 * steps / cus);
-    if (t < best) {
-      best = t;
-      splits = s;
+  return worst;
+}
+
+// How a bf16 forward runs when the caller does not say: `splits` blocks per
+// 32-query item of fwd_small_kernel, or 0 for the persistent 256-query kernel
+// on `ranges` tile ranges.
+struct FwdChoice {
+  int32_t splits;
+  int64_t ranges;
+};
+
+// The fastest of three schedules by times fitted on an MI355X (microseconds,
+// forward alone) over 310 layers of 1 to 57 heads of 64 and 128 and 2e8 to 4e11
+// FLOP: 5 to 7 % rms off each schedule's time, the choice 0.14 % above the best
+// of all schedules on average and 7 % at worst.
+// - Small kernel: blocks of c0 + c1 per step of eight 32-key tiles, dealt out
+//   longest first, c1 up by cx where every CU streams K/V; merging S blocks of
+//   an item adds m0 + m1 S.
+// - Persistent kernel, one range per CU of two tiles at least: p0, pr for the
+//   records of a range per CU, p1 per tile of a range and p2 per piece of the
+//   longest item.
+// - Persistent kernel, whole items, no records and no merge, where the items
+//   are equally long and no more than the CUs: u0 and, per tile, u1 + u2 items
+//   (the clock falls as CUs fill).
+// A schedule has to be better than those before it by 3 %.
+// Measured, small S = 1, 2, 4 / one range per CU / whole items: 2 heads of 128
+// on 270 queries and 4372 keys (and fewer at 2x and 4x) 23.8, 19.7, 16.4 /
+// 41.3 / 74.9 us; 1 head of 64 on 792 and 14256 58.4, 36.0, 24.2 / 48.1 / 181;
+// 18 heads of 128 on 3168 and 3520 166, 205, 264 / 111 / 95.8; 39 heads of 128
+// on 1500 and 1875 111, 153, 228 / 76.2 / 59.9; 50 heads of 128 on 768 and 3072
+// (150 items) - / 78.6 / 74.5, on 768 and 6144 - / 123 / 131.
+// fits: may a schedule's records of that many bytes be had?
+template <class Fits>
+FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>& run_tok, const Schedule& sc,
+                         int64_t n_items, int64_t cus, Fits&& fits) {
+  struct Fit {
+    double a, c0, c1, cx, m0, m1, p0, pr, p1, p2, u0, u1, u2;
+  };
+  const Fit f = p.desc.head_dim == 128
+                    ? Fit{2.1, 4.6, 1.04, 0.25, 3.1, 0.59, 14.0, 12.6, 1.745, 0.44, 15.0, 0.96, 0.0023}
+                    : Fit{2.6, 3.25, 0.89, 0.08, 2.3, 0.46, 9.6, 10.6, 1.14, 0.40, 11.7, 0.91, 0.0005};
+  const double n_cus = static_cast<double>(cus);
+  const int32_t longest = *std::max_element(sc.tiles_per_item.begin(), sc.tiles_per_item.end());
+  const bool equal = *std::min_element(sc.tiles_per_item.begin(), sc.tiles_per_item.end()) == longest;
+  FwdChoice best{0, std::min<int64_t>(cus, std::max<int64_t>(n_items, sc.total_tiles / 2))};
+  if (!fits(range_records(p, std::min(best.ranges, sc.total_tiles)))) best.ranges = std::min<int64_t>(cus, n_items);
+  const double ranges = static_cast<double>(std::max<int64_t>(1, std::min(best.ranges, sc.total_tiles)));
+  const double share = std::max(1.0, static_cast<double>(sc.total_tiles) / ranges);  // tiles of a range
+  double t_best = f.p0 + f.pr * ranges / n_cus + f.p1 * share + f.p2 * longest / share;
+  if (equal && n_items <= cus) {
+    const double t = f.u0 + longest * (f.u1 + f.u2 * static_cast<double>(n_items));
+    if (t < t_best) {
+      best.ranges = n_items;
+      t_best = t;
     }
   }
-  return splits;
+  for (int32_t s = 1; s <= 8; s *= 2) {
+    if (!fits(split_records(p, s))) break;
+    std::vector<BlockRun> runs;
+    double blocks = 0, sum = 0;
+    for (int g : p.order)
+      runs.push_back({int64_t{ceil_div(p.groups[g].q_end - p.groups[g].q_begin, kFwdF32BM)} * p.desc.num_heads * s, 0.0});
+    for (const BlockRun& r : runs) blocks += static_cast<double>(r.n);
+    const double step = f.c1 * (1.0 + f.cx * std::min(1.0, blocks / n_cus));
+    for (size_t i = 0; i < runs.size(); ++i) {
+      int64_t tiles = 0;
+      for (int64_t n : run_tok[p.order[i]]) tiles += (n + 31) / 32;
+      runs[i].cost = f.c0 + step * static_cast<double>((tiles + kSplitWaves * s - 1) / (kSplitWaves * s));
+      sum += static_cast<double>(runs[i].n) * runs[i].cost;
+    }
+    const double fixed = f.a + (s > 1 ? f.m0 + f.m1 * s : 0.0);
+    if (fixed + sum / n_cus >= t_best) continue;  // (also keeps the dealing short)
+    const double t = fixed + dealt_out(runs, cus);
+    if (1.03 * t < t_best) {
+      best.splits = s;
+      t_best = t;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -172,7 +264,6 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
   p.pooled_v_off.assign(G, 0);
   p.pairs_per_head = 0;
   int64_t ws = 0;
-  auto align256 = [](int64_t x) { return (x + 255) / 256 * 256; };
   std::vector<char> win_read(wf.size(), 0);
   bool hist_read = false;
 
@@ -284,21 +375,14 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     n_items += static_cast<int64_t>((p.groups[g].q_end - p.groups[g].q_begin + kFwdBM - 1) / kFwdBM) * d.num_heads;
   }
   p.n_ranges = 1;
-  const int64_t total = make_schedule(p, run_tok).total_tiles;
+  const Schedule whole = make_schedule(p, run_tok);
+  const int64_t total = whole.total_tiles;
   if (slots <= 0) slots = 512;
   // Workspace after the pooled blocks.  Where there is a choice of schedule,
   // one whose records would push a plan past the scratch of the entry point
   // without allocations is passed over if another one fits.
   const int64_t room = MSSA_NOALLOC_SCRATCH_BYTES - ws;
-  auto range_bytes = [&](int64_t n) {  // partial records and range table of n tile ranges
-    return n > 1 ? align256(2 * n * partial_record_floats(d.head_dim) * 4) + align256((n + 1) * 8) : 0;
-  };
-  int64_t items32 = 0;
-  for (const QGroup& g : p.groups)
-    items32 += static_cast<int64_t>((g.q_end - g.q_begin + kFwdF32BM - 1) / kFwdF32BM) * d.num_heads;
-  auto split_bytes = [&](int64_t s) {
-    return s > 1 ? align256(items32 * s * split_record_floats(d.head_dim) * 4) : 0;
-  };
+  auto fits = [&](int64_t bytes) { return room < 0 || bytes <= room; };
   p.partial_off = ws;
   p.range_table_off = 0;
   if (d.dtype == MSSA_F32) {
@@ -311,25 +395,16 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
       for (const Run& r : p.runs[g]) t += (r.n_tok + 31) / 32;
       tiles = std::max(tiles, t);
     }
-    int64_t s = std::max<int64_t>(1, std::min(slots / items32, (tiles + kSplitWaves - 1) / kSplitWaves));
-    if (room >= 0 && split_bytes(s) > room) s = 1;
+    int64_t s = std::max<int64_t>(1, std::min(slots / items_32q(p), (tiles + kSplitWaves - 1) / kSplitWaves));
+    if (!fits(split_records(p, s))) s = 1;
     p.key_splits = static_cast<int32_t>(s);
-    p.partial_bytes = split_bytes(s);
+    p.partial_bytes = split_records(p, s);
   } else {
-    int64_t ranges = attention_blocks;
-    if (attention_blocks <= 0) {
-      p.key_splits = small_layer_splits(p, run_tok, slots);
-      if (room >= 0 && split_bytes(p.key_splits) > room) p.key_splits = 1;
-      // One range per resident block, of two tiles at least: a layer of few
-      // items is split rather than left on few CUs.  Pass of 4 heads of 128
-      // on 15 x 26 (56 items): 167 us at one range per item, 80 at 256
-      // ranges; with under two tiles a range its record costs more than it
-      // saves (2 heads on 10 x 13, 250 tiles: 36 us at 160, 42 at 256).
-      ranges = p.key_splits > 0 ? 1 : std::min<int64_t>(slots, std::max<int64_t>(n_items, total / 2));
-      if (room >= 0 && range_bytes(std::min(ranges, total)) > room) ranges = std::min<int64_t>(slots, n_items);
-    }
-    p.n_ranges = static_cast<int32_t>(std::max<int64_t>(1, std::min(ranges, total)));
-    p.partial_bytes = p.key_splits > 0 ? split_bytes(p.key_splits) : range_bytes(p.n_ranges);
+    FwdChoice c{0, attention_blocks};
+    if (attention_blocks <= 0) c = forward_choice(p, run_tok, whole, n_items, slots, fits);
+    p.key_splits = c.splits;
+    p.n_ranges = c.splits > 0 ? 1 : static_cast<int32_t>(std::max<int64_t>(1, std::min(c.ranges, total)));
+    p.partial_bytes = c.splits > 0 ? split_records(p, c.splits) : range_records(p, p.n_ranges);
     if (p.n_ranges > 1) p.range_table_off = ws + p.partial_bytes - align256((static_cast<int64_t>(p.n_ranges) + 1) * 8);
   }
   p.sched = make_schedule(p, run_tok);

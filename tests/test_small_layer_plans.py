@@ -54,3 +54,31 @@ def test_forward_workspace_holds_nothing_of_the_backward(scales, heads, d, hist)
                 hist_frames=hist, num_heads=heads, head_dim=d, dtype="bf16")
     info = mssa.mssa_plan_create_ex(desc, 1).info()
     assert info["workspace_bytes"] == 2 * sum(_align(n * heads * d * 2) for n in info["pooled_tokens"])
+
+
+def _forward_records(scales, grid, frames, hist, heads, d):
+    """Bytes of a bf16 plan's records: its workspace without the pooled blocks."""
+    desc = dict(num_states=len(scales), scales=scales, grid_h=grid[0], grid_w=grid[1], frames_per_state=frames,
+                sink_frames=0, hist_frames=hist, num_heads=heads, head_dim=d, dtype="bf16")
+    info = mssa.mssa_plan_create(desc).info()
+    return info["workspace_bytes"] - 2 * sum(_align(n * heads * d * 2) for n in info["pooled_tokens"]), info
+
+
+# Layers of one scale on a 24 x 32 grid, three 256-query items a head: whole
+# items where cutting them up would only add records and their merge (300 to
+# 510 items of 12 or 24 tiles; a plan assumes 512 CUs without a device).
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads, hist", [(100, 0), (150, 0), (170, 0), (170, 1)])
+def test_layers_of_many_short_items_stay_whole(heads, hist, d):
+    got, info = _forward_records([1], (24, 32), 1, hist, heads, d)
+    ranges = 3 * heads
+    assert got == _align(2 * ranges * 256 * (d + 2) * 4) + _align((ranges + 1) * 8)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scales, grid, hist, heads, splits", [
+    ([1, 2], (20, 33), 20, 1, 8), ([1, 2, 4], (15, 18), 14, 2, 4), ([1, 2], (10, 12), 10, 2, 1)])
+def test_few_queries_on_a_long_context_split_over_blocks(scales, grid, hist, heads, splits, d):
+    got, info = _forward_records(scales, grid, 1, hist, heads, d)
+    items = sum(-(-(e - b) // 32) for b, e in zip(info["q_begin"], info["q_end"])) * heads
+    assert got == (_align(items * splits * 32 * (d + 2) * 4) if splits > 1 else 0)
