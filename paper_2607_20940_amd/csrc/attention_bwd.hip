@@ -405,14 +405,22 @@ __global__ __launch_bounds__(2 * D) void dq_sum_kernel(BwdArgs a) {
 // accumulation registers, which VALU instructions cannot read; left to itself
 // the compiler put every product's result there and copied S, dP and their
 // starting values back and forth (264 copies per 64 MFMAs).  It does not see
-// these as matrix instructions, so a VALU read of d has to be two other MFMAs
-// away.
+// these as matrix instructions, so the waits it would put around one are the
+// kernel's to keep:
+// - a VALU or memory instruction that touches d comes two MFMAs or 19 cycles of
+//   s_nop later (mfma_done ties the reads of d to that place);
+// - an MFMA comes two instructions after a VALU instruction that writes one of
+//   its operands (mfma_operands where the compiler may have put a copy).
+// tests/test_matrix_core_waits.py checks both in the emitted code.
 __device__ inline void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
 __device__ inline void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
+
+__device__ inline void mfma_done(f32x16& d) { asm volatile("" : "+v"(d)); }
+__device__ inline void mfma_operands() { asm volatile("s_nop 1"); }
 
 // f(I) for I = 0 .. N - 1 as constants (integral_constant), unrolled by the
 // front end: the unroller gives up on the dK/dV kernel's step.
@@ -686,6 +694,7 @@ void dkdv_kernel(BwdArgs a) {
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NDMA + 1 + 8) : "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (i == 0) mfma_operands();
       const bf16x8 av = ring[i % kLead];
       for_constants(std::make_integer_sequence<int, 2>{}, [&](auto KB) __attribute__((always_inline)) {
         constexpr int kb = decltype(KB)::value, sl = 2 * j + kb;  // slot sl of the phase's 2 N
@@ -701,6 +710,10 @@ void dkdv_kernel(BwdArgs a) {
           mfma_v(dp[kb], av, vring[j & 1][kb]);
         else
           mfma_a(dv[j % DB][kb], av, __builtin_bit_cast(bf16x8, pw[kb][j / DB]));
+        if constexpr ((ph == 1 || ph == 3) && sl == 1) {  // two MFMAs behind S's, dP's last
+#pragma unroll
+          for (int b = 0; b < 2; ++b) mfma_done(ph == 1 ? s[b] : dp[b]);
+        }
         if (kb == 0) {
           // operands ahead: the last chunks of a step read the next step's
           // stage, after the barrier
@@ -763,11 +776,13 @@ void dkdv_kernel(BwdArgs a) {
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const bf16x8 av = tr_op(tile(NBUF - 1, 0), i);
+    mfma_operands();
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) mfma_a(dk[i % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][i / DB]));
   }
   wait_vmcnt<0>();  // no transfer into this block's LDS outlives it
-  // the last products have left the matrix core before the accumulators are read
+  // the last products have left the matrix core before the accumulators are
+  // read, and each read is tied to its wait
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
