@@ -410,7 +410,10 @@ __global__ __launch_bounds__(2 * D) void dq_sum_kernel(BwdArgs a) {
 // - a VALU or memory instruction that touches d comes two MFMAs or 19 cycles of
 //   s_nop later (mfma_done ties the reads of d to that place);
 // - an MFMA comes two instructions after a VALU instruction that writes one of
-//   its operands (mfma_operands where the compiler may have put a copy).
+//   its operands (mfma_operands where the compiler may have put a copy);
+// - a VALU instruction that writes a register of the first product's c comes an
+//   MFMA or 16 cycles later (mfma_read keeps c until there; its last registers are
+//   read late).
 // tests/test_matrix_core_waits.py checks both in the emitted code.
 __device__ inline void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
@@ -420,6 +423,7 @@ __device__ inline void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
 }
 
 __device__ inline void mfma_done(f32x16& d) { asm volatile("" : "+v"(d)); }
+__device__ inline void mfma_read(const f32x16& c) { asm volatile("" ::"v"(c)); }
 __device__ inline void mfma_operands() { asm volatile("s_nop 1"); }
 
 // f(I) for I = 0 .. N - 1 as constants (integral_constant), unrolled by the
@@ -710,6 +714,7 @@ void dkdv_kernel(BwdArgs a) {
           mfma_v(dp[kb], av, vring[j & 1][kb]);
         else
           mfma_a(dv[j % DB][kb], av, __builtin_bit_cast(bf16x8, pw[kb][j / DB]));
+        if constexpr ((ph == 0 || ph == 2) && sl == 2) mfma_read(stat);
         if constexpr ((ph == 1 || ph == 3) && sl == 1) {  // two MFMAs behind S's, dP's last
 #pragma unroll
           for (int b = 0; b < 2; ++b) mfma_done(ph == 1 ? s[b] : dp[b]);

@@ -2,10 +2,11 @@
 
 The kernel issues its MFMAs from inline asm, where the compiler does not insert
 the waits the hardware asks for: a result is not to be touched by a VALU or
-memory instruction before the matrix core has written it, and an operand written
-by a VALU instruction is readable two instructions later.  This reads the
-assembly that the build's own flags produce and counts the distances, the loop's
-back edge included."""
+memory instruction before the matrix core has written it, an operand written by
+a VALU instruction is readable two instructions later, and the starting value of
+a product (its third operand) is not to be overwritten while the matrix core
+still reads it.  This reads the assembly that the build's own flags produce and
+counts the distances, the loop's back edge included."""
 
 import os
 import re
@@ -15,7 +16,9 @@ import pytest
 
 from paper_2607_20940_amd import build
 
-MFMAS, CYCLES, OPERAND = 2, 19, 2  # MFMAs or wait states behind a result; wait states before an operand
+MFMAS, CYCLES = 2, 19  # MFMAs or wait states behind a result
+OPERAND = 2            # wait states before an operand
+SOURCE = 16            # wait states, or an MFMA, before a starting value is overwritten
 
 
 def _registers(text):
@@ -45,7 +48,7 @@ def _instructions(lines):
 
 
 def _violations(ins):
-    bad, n_mfma, pos, result, written = [], 0, 0, {}, {}
+    bad, n_mfma, pos, result, written, source = [], 0, 0, {}, {}, {}
     for op, args in ins:
         if "mfma" in op:
             n_mfma += 1
@@ -54,12 +57,16 @@ def _violations(ins):
                     bad.append(("operand", op, args, r))
             for r in _registers(args[0]):
                 result[r] = (n_mfma, pos)
+            for r in _registers(args[3]) - _registers(args[0]):
+                source[r] = (n_mfma, pos)
         elif op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_", "flat_")):
             for r in set().union(set(), *(_registers(a) for a in args)):
                 if r in result and n_mfma - result[r][0] < MFMAS and pos - result[r][1] < CYCLES:
                     bad.append(("result", op, args, r))
             if op.startswith("v_") and args and not op.startswith("v_cmp"):
                 for r in _registers(args[0]):
+                    if r in source and n_mfma == source[r][0] and pos - source[r][1] < SOURCE:
+                        bad.append(("source", op, args, r))
                     written[r] = pos + 1
                     result.pop(r, None)
         pos += int(args[0], 0) + 1 if op == "s_nop" else 1
@@ -101,7 +108,8 @@ def test_the_check_finds_missing_waits():
     mfma = "\tv_mfma_f32_32x32x16_bf16 {0}, v[80:83], v[84:87], {0}"
     a, b, c = (mfma.format(r) for r in ("v[0:15]", "v[16:31]", "a[0:15]"))
     read, store = "\tv_mul_f32_e32 v40, s3, v5", "\tds_write_b32 v41, v17"
-    ok = [[a, b, c, read], [a, "\ts_nop 15", "\ts_nop 2", read], [b, a, c, store],
+    first = "\\tv_mfma_f32_32x32x16_bf16 v[0:15], v[80:83], v[84:87], v[48:63]"
+    ok = [[first, b, "\\tv_mov_b32_e32 v60, v2"], [a, b, c, read], [a, "\ts_nop 15", "\ts_nop 2", read], [b, a, c, store],
           ["\tv_mov_b32_e32 v80, v2", "\ts_nop 1", a]]
     missing = [[a, b, read], [a, read], [b, a, store], [a, "\ts_nop 15", read], [c, "\tv_accvgpr_read_b32 v40, a3"],
                ["\tv_mov_b32_e32 v80, v2", a], ["\tv_mov_b32_e32 v80, v2", "\ts_nop 0", a],
