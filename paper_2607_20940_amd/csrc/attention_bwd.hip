@@ -17,7 +17,7 @@
 // bf16 path (gfx950 matrix cores, v_mfma_f32_32x32x16_bf16, fp32
 // accumulation), five products in two kernels so that no gradient needs
 // atomics:
-//   dkdv_kernel  64 context keys per wave, one wave per SIMD; queries stream in
+//   dkdv_kernel  64 or 32 context keys per wave, one wave per SIMD; queries stream in
 //                32-query stages: S = Q K^T, P (lane = key), dV^T += dO^T P, dP =
 //                dO V^T, dS = P (dP - rowsum), dK^T += Q^T dS, with dO^T, Q^T
 //                from transposing reads, and dS (bf16, the value its own
@@ -415,8 +415,13 @@ __global__ __launch_bounds__(2 * D) void dq_sum_kernel(BwdArgs a) {
 //   MFMA or 16 cycles later (mfma_read keeps c until there; its last registers are
 //   read late).
 // tests/test_matrix_core_waits.py checks both in the emitted code.
+// kAccB: b lies in accumulation registers.
+template <bool kAccB = false>
 __device__ inline void mfma_v(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+  if constexpr (kAccB)
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+  else
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
 __device__ inline void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
@@ -434,19 +439,26 @@ __device__ __forceinline__ void for_constants(std::integer_sequence<int, I...>, 
 }
 
 // d = c + a b, the first product of a chain.
+template <bool kAccB = false>
 __device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
+  if constexpr (kAccB)
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "a"(b), "v"(c));
+  else
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(a), "v"(b), "v"(c));
 }
 
-// dK/dV: a block owns 256 context keys, four waves (one per SIMD, 512
-// registers) of 64 keys each as two 32-key blocks, so that every operand read
-// from LDS feeds two MFMAs.  Queries stream in 32-query stages t; a step is
+// dK/dV: a block owns 128 KB context keys, four waves (one per SIMD, 512
+// registers) of KB 32-key blocks each: with KB = 2 every operand read from LDS
+// feeds two MFMAs, with KB = 1 a layer of few blocks has twice as many and a
+// step is shorter (kv_block_keys in plan.cpp chooses).  Queries stream in
+// 32-query stages t; a step is
 //   A  S_t  = Q_t K^T                (K fragments in registers)
 //   B  dK^T += Q_{t-1}^T dS_{t-1}
-//   C  dP_t = dO_t V^T               (V from the block's 64 KB of LDS)
+//   C  dP_t = dO_t V^T               (KB = 2: V from the block's 64 KB of LDS;
+//                                     KB = 1: V fragments in registers)
 //   D  dV^T += dO_t^T P_t
 // of N = D / 16 chunks each: one operand (row read or transposing read, kLead
-// chunks ahead of its use) and its two MFMAs.  What else there is to do is cut
+// chunks ahead of its use) and its KB MFMAs.  What else there is to do is cut
 // into pieces of about four instructions, one behind every MFMA: P_t =
 // exp2(c S_t) during B and C, dS_t = P_t dP_t during D, its stores and the
 // transfers during A.  A wave alone on its SIMD issues one instruction at a
@@ -470,22 +482,26 @@ __device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c
 // by power; pairs of waves sharing a SIMD, one on the matrix core and one on
 // the softmax, handing P over through LDS behind two barriers per 64 queries:
 // 4.24 - 4.43 ms, 42 %, 6.8 instructions per MFMA beside it where this has 4.1.
-template <int D, bool kQS>
+// Whole backward of small layers with those pairs of waves, KB = 2 and KB = 1: 13
+// heads of 128, 108 queries on 489 keys and two coarser groups 40.1, 53.3 and
+// 41.3 us; 3 heads of 64, 1275 on 5341 and two groups 114, 80.3 and 66.8.
+template <int D, bool kQS, int KB>
 __global__ __launch_bounds__(kBwdKVThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void dkdv_kernel(BwdArgs a) {
   using L = Lay<D>;
   constexpr int N = L::KS, DB = L::DB;                  // chunks per phase, 32-channel blocks
   static_assert(N == 2 * DB, "row and transposing phases have the same chunks");
   constexpr int BQ = kBwdStage;                         // queries per stage
+  constexpr int BK = KB * kBwdKVKeys;                   // keys per block
   constexpr int QT = BQ * 256;                          // bytes of one swizzled tile (256-byte rows)
   constexpr int STB = 2 * QT;                           // Q | dO
   constexpr int kStat = 1024;                           // -lse / scale | unused | -rowsum | unused (256 bytes each, 128 used)
   constexpr int NBUF = 4;
   constexpr int NDMA = 2 * QT / 1024 / 4;               // 1 KB transfers per wave and stage
   constexpr int kStat0 = NBUF * STB, kV0 = kStat0 + NBUF * kStat;  // the stages' statistics, the block's V rows
-  constexpr int kDump = kV0 + kBwdK * 256;              // 1 KB that nothing reads
+  constexpr int kDump = kV0 + (KB == 2 ? BK * 256 : 0); // 1 KB that nothing reads
   constexpr int kLead = 4;                              // chunks an operand is read ahead
-  static_assert(BQ == 32 && NDMA == 4 && kBwdK == 256 && 4 * N % kLead == 0, "stage shape");
+  static_assert(BQ == 32 && NDMA == 4 && kBwdKVKeys == 128 && (KB == 1 || KB == 2) && 4 * N % kLead == 0, "stage shape");
   __shared__ __attribute__((aligned(16))) char lds[kDump + 1024];
 
   const int b = blockIdx.x;
@@ -501,15 +517,15 @@ void dkdv_kernel(BwdArgs a) {
   const int n = lane & 31, hh = lane >> 5;
   const int64_t ld = a.ld, hoff = static_cast<int64_t>(head) * D;
   const float c = a.scale_log2e;
-  const int key0 = kt * kBwdK + wave * 64 + n;  // this lane's keys: key0, key0 + 32
+  const int key0 = kt * BK + wave * 32 * KB + n;  // this lane's keys: key0 + 32 kb
 
   // Byte offset, in the tiles of a 32-query block, of the lane's dS of each
   // key: the key's 64-key stage (its run's stages, as the dQ kernel walks
   // them), slot and the lane's 8 queries of each tile half.  Keys past the
   // context point past the range: the range check drops their stores.
-  uint32_t ds_voff[2];
+  uint32_t ds_voff[KB];
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
+  for (int kb = 0; kb < KB; ++kb) {
     const int key = key0 + kb * 32;
     const bool ok = key < G.n_kv;
     int j = ok ? key : 0, st = 0, r = 0;
@@ -567,38 +583,47 @@ void dkdv_kernel(BwdArgs a) {
 #pragma unroll
     for (int i = 0; i <= NDMA; ++i) issue(t, t, i);
   // fewer stages than buffers: the others hold the last stage's queries
-  if (wave < 2)
+  if (KB == 2 && wave < 2)
     for (int t = nst; t < NBUF; ++t)
 #pragma unroll
       for (int i = 0; i <= NDMA; ++i) issue(nst - 1, t, i);
-  bf16x8 kf[2][N];
+  bf16x8 kf[KB][N], vf[KB == 1 ? N : 1];  // KB = 1: V fragments too, in accumulation registers
   {
-    constexpr int CH = D / 8, RP = kBwdKVThreads / CH, NV = kBwdK / RP;  // 16-byte chunks per row, rows per pass, passes
+    constexpr int CH = D / 8, RP = kBwdKVThreads / CH, NV = BK / RP;  // 16-byte chunks per row, rows per pass, passes
     bf16x8 vrow[NV];
+    if constexpr (KB == 1) {
+      const __bf16* vp = ctx_row<__bf16>(G, key0, true, ld);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const __bf16* vp = ctx_row<__bf16>(G, kt * kBwdK + i * RP + tid / CH, true, ld);
+      for (int ks = 0; ks < N; ++ks)
+        vf[ks] = vp ? *reinterpret_cast<const bf16x8*>(vp + hoff + hh * 8 + ks * 16) : bf16x8{};
+    }
+#pragma unroll
+    for (int i = 0; i < NV && KB == 2; ++i) {
+      const __bf16* vp = ctx_row<__bf16>(G, kt * BK + i * RP + tid / CH, true, ld);
       vrow[i] = vp ? *reinterpret_cast<const bf16x8*>(vp + hoff + tid % CH * 8) : bf16x8{};
     }
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < KB; ++kb) {
       const __bf16* kp = ctx_row<__bf16>(G, key0 + kb * 32, false, ld);
 #pragma unroll
       for (int ks = 0; ks < N; ++ks)
         kf[kb][ks] = kp ? *reinterpret_cast<const bf16x8*>(kp + hoff + hh * 8 + ks * 16) : bf16x8{};
     }
     // the queries of stage -1 (multiplied by dS = 0 in the first step)
-    for (int i = nst < NBUF ? QT / 16 : tid; i < QT / 16; i += kBwdKVThreads)
+    for (int i = KB == 2 && nst < NBUF ? QT / 16 : tid; i < QT / 16; i += kBwdKVThreads)
       reinterpret_cast<bf16x8*>(lds + (NBUF - 1) * STB)[i] = bf16x8{};
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
+    for (int i = 0; i < NV && KB == 2; ++i)
       *reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(lds + kV0) + swz(i * RP + tid / CH, tid % CH * 8)) = vrow[i];
   }
   wait_vmcnt<0>();  // the transfers too, which the compiler does not count
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-    for (int ks = 0; ks < N; ++ks) asm volatile("" : "+v"(kf[kb][ks]));
+    for (int ks = 0; ks < N; ++ks) {
+      asm volatile("" : "+v"(kf[kb][ks]));
+      if (KB == 1) asm volatile("" : "+a"(vf[ks]));
+    }
   __syncthreads();
 
   // Lane offsets (elements) of row reads and of transposing reads.
@@ -610,7 +635,7 @@ void dkdv_kernel(BwdArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int h = 0; h < 2; ++h) t_rd[db][h] = swz(t_lane + 8 * h, db * 32 + t_col);
-  const __bf16* const Vw = reinterpret_cast<const __bf16*>(lds + kV0) + wave * 64 * 128;
+  const __bf16* const Vw = reinterpret_cast<const __bf16*>(lds + kV0) + wave * 32 * KB * 128;
   auto tile = [&](int buf, int which) { return reinterpret_cast<const __bf16*>(lds + buf * STB + which * QT); };  // 0: Q, 1: dO
   auto row_op = [&](const __bf16* x, int ks) { return *reinterpret_cast<const bf16x8*>(x + (r_rd ^ (ks * 16))); };
   auto tr_op = [&](const __bf16* x, int i) {  // i = (16-row half, channel block)
@@ -620,10 +645,10 @@ void dkdv_kernel(BwdArgs a) {
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  f32x16 dk[DB][2], dv[DB][2], s[2], dp[2], stat;
-  i32x4 pw[2][2], ds[2][2];  // P_t and dS packed as B operands, [key block][16-query half]
+  f32x16 dk[DB][KB], dv[DB][KB], s[KB], dp[KB], stat;
+  i32x4 pw[KB][2], ds[KB][2];  // P_t and dS packed as B operands, [key block][16-query half]
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
+  for (int kb = 0; kb < KB; ++kb) {
 #pragma unroll
     for (int db = 0; db < DB; ++db) dk[db][kb] = dv[db][kb] = f32x16{};
     ds[kb][0] = ds[kb][1] = i32x4{};
@@ -641,7 +666,7 @@ void dkdv_kernel(BwdArgs a) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(int, bf16x2{static_cast<__bf16>(x), static_cast<__bf16>(y)});
   };
-  // Pair x (of 16) of the lane's 32 elements: key block x / 8, elements e, e + 1.
+  // Pair x (of 8 KB) of the lane's elements: key block x / 8, elements e, e + 1.
   // P stays in s in fp32 for dS.
   auto p_pair = [&](int x) {
     const int kb = x >> 3, e = (x & 7) * 2;
@@ -673,7 +698,7 @@ void dkdv_kernel(BwdArgs a) {
     }
   };
 
-  bf16x8 ring[kLead], vring[2][2];
+  bf16x8 ring[kLead], vring[2][KB];
   // Operand of chunk i (0 .. 4 N - 1; 4 N .. : the next step's) of a step on buffer B.
   auto operand = [&](auto B, int i) {
     constexpr int cur = decltype(B)::value, prev = (cur + NBUF - 1) % NBUF, next = (cur + 1) % NBUF;
@@ -691,17 +716,17 @@ void dkdv_kernel(BwdArgs a) {
       constexpr int i = decltype(I)::value, ph = i / N, j = i % N;
       if (i == 3 * N) {
         // stage t + 1 has arrived: younger than its transfers (in A of the
-        // previous step) are that step's four stores, stage t + 2's transfers
-        // and this step's four stores
+        // previous step) are that step's 2 KB stores, stage t + 2's transfers
+        // and this step's 2 KB stores
         // (operand reads stay in flight across the barrier: no buffer they
         // read is overwritten before the next one)
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NDMA + 1 + 8) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NDMA + 1 + 4 * KB) : "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
       if (i == 0) mfma_operands();
       const bf16x8 av = ring[i % kLead];
-      for_constants(std::make_integer_sequence<int, 2>{}, [&](auto KB) __attribute__((always_inline)) {
-        constexpr int kb = decltype(KB)::value, sl = 2 * j + kb;  // slot sl of the phase's 2 N
+      for_constants(std::make_integer_sequence<int, KB>{}, [&](auto KBI) __attribute__((always_inline)) {
+        constexpr int kb = decltype(KBI)::value, sl = KB * j + kb;  // slot sl of the phase's KB N
         if constexpr (ph == 0 && j == 0)
           mfma_first(s[kb], av, kf[kb][0], stat);
         else if constexpr (ph == 0)
@@ -709,27 +734,39 @@ void dkdv_kernel(BwdArgs a) {
         else if constexpr (ph == 1)
           mfma_a(dk[j % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][j / DB]));
         else if constexpr (ph == 2 && j == 0)
-          mfma_first(dp[kb], av, vring[0][kb], stat);
+          mfma_first<KB == 1>(dp[kb], av, KB == 1 ? vf[0] : vring[0][kb], stat);
         else if constexpr (ph == 2)
-          mfma_v(dp[kb], av, vring[j & 1][kb]);
+          mfma_v<KB == 1>(dp[kb], av, KB == 1 ? vf[KB == 1 ? j : 0] : vring[j & 1][kb]);
         else
           mfma_a(dv[j % DB][kb], av, __builtin_bit_cast(bf16x8, pw[kb][j / DB]));
-        if constexpr ((ph == 0 || ph == 2) && sl == 2) mfma_read(stat);
+        if constexpr ((ph == 0 || ph == 2) && sl == KB) mfma_read(stat);
         if constexpr ((ph == 1 || ph == 3) && sl == 1) {  // two MFMAs behind S's, dP's last
 #pragma unroll
-          for (int b = 0; b < 2; ++b) mfma_done(ph == 1 ? s[b] : dp[b]);
+          for (int b = 0; b < KB; ++b) mfma_done(ph == 1 ? s[b] : dp[b]);
         }
         if (kb == 0) {
           // operands ahead: the last chunks of a step read the next step's
           // stage, after the barrier
           ring[i % kLead] = operand(B, i + kLead);
-          if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][0] = v_op(i + 2 - 2 * N, 0);
-        } else {
-          if (i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][1] = v_op(i + 2 - 2 * N, 1);
+        }
+        if (KB == 2 && i >= 2 * N - 2 && i < 3 * N - 2) vring[i & 1][kb] = v_op(i + 2 - 2 * N, kb);
+        if (kb == KB - 1) {
           if (ph == 1 && j == N - 2) load_stat(cur, 2);
           if (ph == 3 && j == N - 2) load_stat(next, 0);
         }
-        if constexpr (ph == 0) {
+        if constexpr (ph == 0 && KB == 1) {
+          // the pieces in this order, spread over the slots
+          constexpr int kPieces = NDMA + 3;
+          for_constants(std::make_integer_sequence<int, kPieces>{}, [&](auto P) __attribute__((always_inline)) {
+            constexpr int p = decltype(P)::value;
+            if constexpr (p * N / kPieces == sl) {
+              if (p <= NDMA)
+                issue(t + 2, t + 2, p);
+              else
+                ds_store(t - 1, 0, p - NDMA - 1);
+            }
+          });
+        } else if constexpr (ph == 0) {
           if (sl <= NDMA) issue(t + 2, t + 2, sl);  // before the stores: the wait above counts on it
           if (N == 4 && sl == 2 * N - 2) {
             ds_store(t - 1, 0, 0);
@@ -741,17 +778,17 @@ void dkdv_kernel(BwdArgs a) {
           }
           if (N > 4 && sl >= 2 * N - 8 && sl % 2 == 0) ds_store(t - 1, (sl - (2 * N - 8)) / 4, (sl - (2 * N - 8)) / 2 % 2);
         } else if constexpr (ph == 3) {
-          spread(std::integral_constant<int, sl>{}, std::integral_constant<int, 2 * N>{}, std::integral_constant<int, 16>{}, ds_pair);
+          spread(std::integral_constant<int, sl>{}, std::integral_constant<int, KB * N>{}, std::integral_constant<int, 8 * KB>{}, ds_pair);
         } else {
-          spread(std::integral_constant<int, (ph - 1) * 2 * N + sl>{}, std::integral_constant<int, 4 * N>{},
-                 std::integral_constant<int, 16>{}, p_pair);
+          spread(std::integral_constant<int, (ph - 1) * KB * N + sl>{}, std::integral_constant<int, 2 * KB * N>{},
+                 std::integral_constant<int, 8 * KB>{}, p_pair);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
     });
     // dS is due here, not in the next step's block
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(ds[kb][h]));
   };
@@ -763,33 +800,38 @@ void dkdv_kernel(BwdArgs a) {
   load_stat(0, 0);
 #pragma unroll
   for (int i = 0; i < kLead; ++i) ring[i] = operand(I0{}, i);
-  // Stages past the last one, which fill the round, add nothing (a way out
-  // between the steps made the compiler move the accumulators about).
+  // KB = 2: stages past the last one, which fill the round, add nothing (a way
+  // out between the steps made the compiler move the accumulators about, which
+  // take all the registers there).
   int t = 0;
-  do {  // a group has queries
-    step(I0{}, t);
-    step(I1{}, t + 1);
-    step(I2{}, t + 2);
-    step(I3{}, t + 3);
-    t += NBUF;
-  } while (t < nst);
-  // dS of the round's last stage, and its dK
+  while (true) {  // a group has queries
+    step(I0{}, t++);
+    if (KB == 1 && t >= nst) break;
+    step(I1{}, t++);
+    if (KB == 1 && t >= nst) break;
+    step(I2{}, t++);
+    if (KB == 1 && t >= nst) break;
+    step(I3{}, t++);
+    if (t >= nst) break;
+  }
+  // dS of the last stage, and its dK
+  const int last = KB == 1 ? (t - 1) & (NBUF - 1) : NBUF - 1;
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
     for (int h = 0; h < 2; ++h) ds_store(t - 1, kb, h);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    const bf16x8 av = tr_op(tile(NBUF - 1, 0), i);
+    const bf16x8 av = tr_op(tile(last, 0), i);
     mfma_operands();
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) mfma_a(dk[i % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][i / DB]));
+    for (int kb = 0; kb < KB; ++kb) mfma_a(dk[i % DB][kb], av, __builtin_bit_cast(bf16x8, ds[kb][i / DB]));
   }
   wait_vmcnt<0>();  // no transfer into this block's LDS outlives it
   // the last products have left the matrix core before the accumulators are
   // read, and each read is tied to its wait
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
       asm volatile("s_nop 15" : "+a"(dk[db][kb]));
@@ -797,7 +839,7 @@ void dkdv_kernel(BwdArgs a) {
     }
 
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
+  for (int kb = 0; kb < KB; ++kb) {
     const int key = key0 + kb * 32;
     if (key < G.n_kv) {
       const int64_t off = static_cast<int64_t>(key) * ld + hoff + 4 * hh;
@@ -887,14 +929,25 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
   if (!bf16) return launch_bwd_f32(a, dq_blocks, kv_blocks, head_dim, stream);
   // dK/dV first: it writes the dS tiles the dQ kernel reads.
   if (kv_blocks > 0) {
+    auto go = [&](auto d, auto qs, auto kb) {
+      hipLaunchKernelGGL((dkdv_kernel<decltype(d)::value, decltype(qs)::value, decltype(kb)::value>), dim3(kv_blocks),
+                         dim3(kBwdKVThreads), 0, stream, a);
+    };
+    auto pick = [&](auto d, auto qs) {
+      if (a.kv_keys == kBwdKVKeys)
+        go(d, qs, std::integral_constant<int, 1>{});
+      else
+        go(d, qs, std::integral_constant<int, 2>{});
+    };
+    if (a.kv_keys != kBwdKVKeys && a.kv_keys != 2 * kBwdKVKeys) return hipErrorInvalidValue;
     if (head_dim == 128 && a.q_prescaled)
-      hipLaunchKernelGGL((dkdv_kernel<128, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+      pick(std::integral_constant<int, 128>{}, std::true_type{});
     else if (head_dim == 128)
-      hipLaunchKernelGGL((dkdv_kernel<128, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+      pick(std::integral_constant<int, 128>{}, std::false_type{});
     else if (a.q_prescaled)
-      hipLaunchKernelGGL((dkdv_kernel<64, true>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+      pick(std::integral_constant<int, 64>{}, std::true_type{});
     else
-      hipLaunchKernelGGL((dkdv_kernel<64, false>), dim3(kv_blocks), dim3(kBwdKVThreads), 0, stream, a);
+      pick(std::integral_constant<int, 64>{}, std::false_type{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

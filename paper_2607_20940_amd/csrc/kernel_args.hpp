@@ -75,14 +75,14 @@ constexpr int64_t split_record_floats(int head_dim) { return 32 * static_cast<in
 
 // ---------------------------------------------------------------- backward
 
-// bf16 backward kernels: 8 waves, 32 queries (dQ kernel) or 32 keys (dK/dV
-// kernel) per wave or wave pair; the other operands stream through LDS in
+// bf16 backward kernels: 8 waves of 32 queries (dQ kernel), 4 waves of 32 or 64
+// keys, one per SIMD (dK/dV kernel); the other operand streams through LDS in
 // stages.
 constexpr int kBwdQ = 256;     // dQ kernel: queries per block (8 waves x 32)
 constexpr int kBwdQThreads = 512;   // dQ kernel: 8 waves, two per SIMD
 constexpr int kBwdKS = 64;     // dQ kernel: keys per LDS stage (and per dS tile)
-constexpr int kBwdK = 256;     // dK/dV kernel: keys per block (4 waves x 64)
-constexpr int kBwdKVThreads = 256;  // dK/dV kernel: 4 waves, one per SIMD
+constexpr int kBwdKVKeys = 128;     // dK/dV kernel: keys per block with 32 a wave, twice as many with 64 (BwdArgs::kv_keys)
+constexpr int kBwdKVThreads = 256;  // dK/dV kernel: 4 waves
 constexpr int kBwdQS = 64;     // dS tiles: queries are rounded up to this
 constexpr int kBwdStage = 32;  // dK/dV kernel: queries per LDS stage
 constexpr int64_t kBwdDsBudget = int64_t(8) << 30;  // bytes of dS tiles held at once (whole heads, at least one)
@@ -124,6 +124,8 @@ struct BwdArgs {
   float scale_log2e;
   int32_t q_prescaled;      // queries arrive multiplied by scale * log2(e)
   int32_t dq_blocks;        // bf16 dQ kernel: blocks per split (set by the launcher)
+  int32_t kv_keys;          // bf16 dK/dV kernel: keys per block
+  int32_t pad;
   BwdGroupArgs groups[kMaxGroups];  // longest query range first
 };
 static_assert(sizeof(BwdArgs) <= 4096, "kernel argument block");

@@ -40,35 +40,48 @@ int64_t split_records(const Plan& p, int64_t s) {
 }
 
 // Blocks of one cost (microseconds), and the time of blocks dealt out in this
-// order over `cus` CUs, one at a time on each: an XCD's CUs share a contiguous
-// eighth of them (xcd_remap of the kernels).
+// order over an XCD's CUs, one at a time on each.
+constexpr int64_t kXcds = 8;
 struct BlockRun {
   int64_t n;
   double cost;
 };
 double dealt_out(const std::vector<BlockRun>& runs, int64_t cus) {
-  constexpr int64_t kXcds = 8;
+  cus = std::max<int64_t>(1, cus);
+  std::map<double, int64_t> busy{{0.0, cus}};  // CUs by the time they are free
+  double rounds = 0;                           // of whole rounds, on top of it
+  for (const BlockRun& r : runs) {
+    int64_t left = r.n;
+    if (left >= 2 * cus) {
+      rounds += r.cost * static_cast<double>(left / cus - 1);
+      left = left % cus + cus;
+    }
+    while (left > 0) {
+      const auto [t, free] = *busy.begin();
+      const int64_t k = std::min(left, free);
+      busy.erase(busy.begin());
+      if (free > k) busy[t] += free - k;
+      busy[t + r.cost] += k;
+      left -= k;
+    }
+  }
+  return rounds + busy.rbegin()->first;
+}
+
+// Blocks of a grid of which every XCD has a contiguous eighth: the slowest XCD.
+double dealt_in_eighths(const std::vector<BlockRun>& runs, int64_t cus) {
   int64_t blocks = 0;
   for (const BlockRun& r : runs) blocks += r.n;
   double worst = 0;
   for (int64_t x = 0; x < kXcds; ++x) {
     const int64_t lo = blocks * x / kXcds, hi = blocks * (x + 1) / kXcds;
-    std::map<double, int64_t> busy{{0.0, std::max<int64_t>(1, cus / kXcds)}};  // CUs by the time they are free
+    std::vector<BlockRun> mine;
     int64_t first = 0;
     for (const BlockRun& r : runs) {
-      int64_t left = std::min(hi, first + r.n) - std::max(lo, first);
+      mine.push_back({std::min(hi, first + r.n) - std::max(lo, first), r.cost});
       first += r.n;
-      while (left > 0) {
-        const auto it = busy.begin();
-        const auto [t, free] = *it;
-        const int64_t k = std::min(left, free);
-        busy.erase(it);
-        if (free > k) busy[t] += free - k;
-        busy[t + r.cost] += k;
-        left -= k;
-      }
     }
-    if (hi > lo) worst = std::max(worst, busy.rbegin()->first);
+    worst = std::max(worst, dealt_out(mine, cus / kXcds));
   }
   return worst;
 }
@@ -142,13 +155,45 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
     }
     const double fixed = f.a + (s > 1 ? f.m0 + f.m1 * s : 0.0);
     if (fixed + sum / n_cus >= t_best) continue;  // (also keeps the dealing short)
-    const double t = fixed + dealt_out(runs, cus);
+    const double t = fixed + dealt_in_eighths(runs, cus);
     if (1.03 * t < t_best) {
       best.splits = s;
       t_best = t;
     }
   }
   return best;
+}
+
+// Keys per block of the bf16 dK/dV kernel: 128 (32 a wave) where there are few
+// blocks or few queries, else 256 (64 a wave: two MFMAs per operand read).  The
+// faster one by times fitted on an MI355X over 150 layers of 1 to 40 heads and
+// 1e8 to 1.5e12 FLOP: a block costs its start and its 32-query steps, which with
+// 64 keys a wave run in fours; each XCD has an eighth of every group's blocks.
+// Backward with 128 / 256 keys: 13 heads of 128, 108 queries on 489 keys and two
+// small groups 41.3 / 53.3 us; 3 heads of 64, 1275 on 5341 and two groups 66.8 /
+// 80.3; 14 heads of 64, 832 on 4160 87.4 / 81.4; 3 heads of 128, 6048 on 11088
+// 401 / 336.  The choice was 2.4 % above the better one at worst.
+int32_t kv_block_keys(const Plan& p, int64_t cus) {
+  const bool d128 = p.desc.head_dim == 128;
+  double best = 0;
+  int32_t keys = 0;
+  for (int32_t kb = 1; kb <= 2; ++kb) {
+    const double start = kb == 1 ? (d128 ? 8.0 : 4.4) : (d128 ? 16.9 : 9.1);
+    const double step = kb == 1 ? (d128 ? 0.59 : 0.435) : (d128 ? 0.96 : 0.657);
+    std::vector<BlockRun> runs;
+    for (int g : p.order) {
+      const int64_t n = (p.groups[g].n_kv + kb * kBwdKVKeys - 1) / (kb * kBwdKVKeys) * p.bwd_ds_heads;
+      int64_t steps = ceil_div(p.groups[g].q_end - p.groups[g].q_begin, kBwdStage);
+      if (kb == 2) steps = (steps + 3) / 4 * 4;
+      runs.push_back({(n + kXcds - 1) / kXcds, start + step * static_cast<double>(steps)});
+    }
+    const double t = dealt_out(runs, cus / kXcds);
+    if (keys == 0 || t < best) {
+      best = t;
+      keys = kb * kBwdKVKeys;
+    }
+  }
+  return keys;
 }
 
 }  // namespace
@@ -437,6 +482,7 @@ mssa_status build_plan(const mssa_plan_desc& d, int slots, int attention_blocks,
     }
     p.bwd_ds_heads = static_cast<int32_t>(
         std::max<int64_t>(1, std::min<int64_t>(d.num_heads, kBwdDsBudget / std::max<int64_t>(1, per_head))));
+    p.bwd_kv_keys = kv_block_keys(p, slots);
     // dQ of a layer with few 256-query blocks: splits of at least six 64-key
     // stages of the longest context, and of enough stages of the group's own
     // for a split's sum to lie in their dS tiles.

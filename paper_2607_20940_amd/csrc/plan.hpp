@@ -131,6 +131,7 @@ struct Plan {
   std::vector<int64_t> bwd_ds_off;      // bytes, per group
   std::vector<int32_t> bwd_ds_stages;   // 64-key stages of the group's runs
   std::vector<int32_t> bwd_ds_qblocks;  // 32-query blocks, rounded up to an even count
+  int32_t bwd_kv_keys = 0;              // keys per block of the bf16 dK/dV kernel
   std::vector<int32_t> bwd_dq_splits;   // blocks that share the context of 256 queries in the bf16 dQ kernel
   int64_t bwd_workspace_bytes;
   std::vector<ScatterJob> scatter_jobs;

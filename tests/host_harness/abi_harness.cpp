@@ -118,6 +118,9 @@ hipError_t scratch_address(void** out) {
 
 int forward_blocks_per_cu(int) { return 1; }
 
+// What the last forward and backward launches were given.
+int g_key_splits = 0, g_ranges = 0, g_kv_keys = 0;
+
 hipError_t launch_pool(const PoolArgs& a, int n_blocks, bool bf16, hipStream_t) {
   const int64_t rb = a.ld * (bf16 ? 2 : 4);
   if (a.chunks_per_tok * 16 != rb) failure("pool: chunks_per_tok");
@@ -148,6 +151,8 @@ hipError_t launch_pool(const PoolArgs& a, int n_blocks, bool bf16, hipStream_t) 
 
 hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t) {
   const int64_t eb = bf16 ? 2 : 4, rb = a.ld * eb;
+  g_key_splits = a.key_splits;
+  g_ranges = a.n_ranges;
   if (a.ld != int64_t{a.num_heads} * head_dim) failure("forward: ld");
   check_range(a.q, a.n_q * rb, "forward q");
   check_range(a.out, a.n_q * rb, "forward out");
@@ -200,6 +205,7 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
   const int64_t rb = a.ld * (bf16 ? 2 : 4);
   if (head_dim <= 0 || a.ld % head_dim != 0) failure("backward: ld");
   const int64_t H = a.ld / head_dim;
+  g_kv_keys = a.kv_keys;
   if (a.head0 == 0) g_bwd_next_head = 0;
   if (a.num_heads <= 0 || a.head0 != g_bwd_next_head || a.head0 + a.num_heads > H)
     failure("backward: launch heads");
@@ -227,6 +233,10 @@ hipError_t launch_bwd(const BwdArgs& a, int dq_blocks, int kv_blocks, int head_d
     if (G.dq_block_begin != qblocks || G.kv_block_begin != kblocks) failure("backward: block ranges");
     qblocks += int64_t{G.n_qblocks} * a.num_heads;
     kblocks += int64_t{G.n_kblocks} * a.num_heads;
+    if (bf16 ? (a.kv_keys != kBwdKVKeys && a.kv_keys != 2 * kBwdKVKeys) ||
+                   G.n_kblocks != ceil_div(int64_t{G.n_kv}, int64_t{a.kv_keys})
+             : G.n_kblocks != ceil_div(int64_t{G.n_kv}, int64_t{kBwdF32}))
+      failure("backward: key blocks");
     if (bf16) {
       // the dS tiles of every head of the launch, every 32-query block the
       // dK/dV kernel's 64-query stages write, every 64-key stage of the runs
@@ -580,6 +590,37 @@ int main(int argc, char** argv) {
   for (const auto& c : named) {
     g_case = c.first;
     exercise(c.second, 0);
+  }
+  // The kernels that tests of their own are there for are the ones the plans of
+  // those tests take on 256 CUs: 32-query items (blocks per item; 0: persistent
+  // kernel) and keys per dK/dV block.
+  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1};
+  const struct {
+    const char* what;
+    mssa_plan_desc d;
+    int splits, keys;
+  } chosen[] = {
+      {"preview layer", make_desc(5, s12, 10, 13, 3, 1, 2, 2, 128, MSSA_BF16, 0), 1, 128},
+      {"1.3B layer", named[1].second, 0, 256},
+      {"key blocks: one coarse stage, 64", make_desc(3, s114, 16, 24, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks: one coarse stage, 128", make_desc(3, s114, 16, 24, 1, 0, 1, 256, 128, MSSA_BF16, 0), -1, 256},
+      {"key blocks: two coarse stages, 64", make_desc(3, s114, 23, 34, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks: two coarse stages, 128", make_desc(3, s114, 23, 34, 1, 0, 1, 256, 128, MSSA_BF16, 0), -1, 256},
+      {"key blocks: six coarse stages, 64", make_desc(2, t12, 24, 32, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks: six coarse stages, 128", make_desc(2, t12, 24, 32, 1, 0, 1, 256, 128, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 1 stage, 64", make_desc(4, s1114, 16, 32, 1, 1, 0, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 1 stage, 128", make_desc(4, s1114, 16, 32, 1, 1, 0, 256, 128, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 2 stages, 64", make_desc(3, s114, 32, 32, 1, 1, 0, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 2 stages, 128", make_desc(3, s114, 32, 32, 1, 1, 0, 256, 128, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 26 stages, 64", make_desc(2, s11, 16, 26, 1, 1, 0, 256, 64, MSSA_BF16, 0), -1, 256},
+      {"key blocks, infinite key: 26 stages, 128", make_desc(2, s11, 16, 26, 1, 1, 0, 256, 128, MSSA_BF16, 0), -1, 256},
+  };
+  for (const auto& c : chosen) {
+    g_case = c.what;
+    exercise(c.d, 0);
+    if (c.splits >= 0 && mssa::g_key_splits != c.splits) failure("forward kernel chosen");
+    if (mssa::g_kv_keys != c.keys) failure("keys per dK/dV block chosen");
+    g_checks += 2;
   }
   g_case = "1.3B layer, 7 attention blocks";
   exercise(named[1].second, 7);
