@@ -888,10 +888,11 @@ mssa::PatchArgs tier_patch(const TierGroup& t, const mssa_tier_desc* tier, void*
 }
 
 // The tiers that move their own patches, in one launch.
-mssa_status launch_tiers(std::vector<mssa::GemmArgs>& ga, const char* what, hipStream_t hs) {
-  if (ga.empty()) return MSSA_OK;
-  for (size_t i = 0; i + 1 < ga.size(); ++i) ga[i].next = &ga[i + 1];
-  return check_device(mssa::launch_gemm_split(ga[0], nullptr, hs), what);
+mssa_status launch_tiers(mssa::TierArgs& a, bool embed, const char* what, hipStream_t hs) {
+  if (a.n == 0) return MSSA_OK;
+  const int64_t blocks = mssa::tier_blocks(a, embed);
+  if (blocks > 0x7fffffff) return fail(MSSA_ERR_UNSUPPORTED, what, "grid too large");
+  return check_device(mssa::launch_tiers(a, blocks, embed, hs), what);
 }
 
 }  // namespace
@@ -922,39 +923,43 @@ mssa_status mssa_patch_embed(mssa_plan plan, const mssa_tier_desc* tier, const v
       if (!w_embed[g] || !b_embed[g] || !aligned16(w_embed[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
-    std::vector<mssa::PatchArgs> patch(tg.size());
-    std::vector<mssa::GemmArgs> fused;
+    mssa::TierArgs fused{};
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
-      mssa::PatchArgs& pa = patch[g];
-      pa = tier_patch(t, tier, const_cast<void*>(latent), static_cast<char*>(workspace) + t.rows_off, H, W);
+      const mssa::PatchArgs pa =
+          tier_patch(t, tier, const_cast<void*>(latent), static_cast<char*>(workspace) + t.rows_off, H, W);
+      mssa::TierProblem tp{};
+      tp.w = w_embed[g];
+      tp.bias = b_embed[g];
+      tp.y = static_cast<char*>(tokens) + static_cast<int64_t>(Q.q_begin) * hid * 2;
+      tp.patch = pa;
+      tp.M = Q.q_end - Q.q_begin;
+      tp.N = hid;
+      tp.K = t.kp;
+      if (mssa::tier_fused(tp, true)) {
+        fused.g[fused.n++] = tp;
+        continue;
+      }
       mssa::GemmArgs ga{};
       ga.y0_scale = 1.f;
       ga.x = pa.rows;
-      ga.w = w_embed[g];
-      ga.bias = b_embed[g];
-      ga.y[0] = static_cast<char*>(tokens) + static_cast<int64_t>(Q.q_begin) * hid * 2;
-      ga.M = Q.q_end - Q.q_begin;
-      ga.N = hid;
-      ga.K = t.kp;
+      ga.w = tp.w;
+      ga.bias = tp.bias;
+      ga.y[0] = tp.y;
+      ga.M = tp.M;
+      ga.N = tp.N;
+      ga.K = tp.K;
       ga.split = hid;
       ga.ldx = t.kp;
       ga.ldy = hid;
-      ga.fuse = mssa::kFuseEmbed;
-      ga.patch = &pa;
-      if (mssa::tier_fused(ga)) {
-        fused.push_back(ga);
-        continue;
-      }
-      ga.fuse = 0;
       s = check_device(mssa::launch_patchify(pa, hs), "patchify launch");
       if (s != MSSA_OK) return s;
       s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
                        "patch embedding GEMM launch");
       if (s != MSSA_OK) return s;
     }
-    return launch_tiers(fused, "patch embedding launch", hs);
+    return launch_tiers(fused, true, "patch embedding launch", hs);
   });
 }
 
@@ -976,39 +981,42 @@ mssa_status mssa_patch_unembed(mssa_plan plan, const mssa_tier_desc* tier, const
       if (!w_out[g] || !b_out[g] || !aligned16(w_out[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
-    std::vector<mssa::PatchArgs> patch(tg.size());
-    std::vector<mssa::GemmArgs> fused;
+    mssa::TierArgs fused{};
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
-      mssa::PatchArgs& pa = patch[g];
-      pa = tier_patch(t, tier, latent, static_cast<char*>(workspace) + t.rows_off, H, W);
+      const mssa::PatchArgs pa = tier_patch(t, tier, latent, static_cast<char*>(workspace) + t.rows_off, H, W);
+      mssa::TierProblem tp{};
+      tp.x = static_cast<const char*>(tokens) + static_cast<int64_t>(Q.q_begin) * hid * 2;
+      tp.w = w_out[g];
+      tp.bias = b_out[g];
+      tp.patch = pa;
+      tp.M = Q.q_end - Q.q_begin;
+      tp.N = t.kp;
+      tp.K = hid;
+      if (mssa::tier_fused(tp, false)) {
+        fused.g[fused.n++] = tp;
+        continue;
+      }
       mssa::GemmArgs ga{};
       ga.y0_scale = 1.f;
-      ga.x = static_cast<const char*>(tokens) + static_cast<int64_t>(Q.q_begin) * hid * 2;
-      ga.w = w_out[g];
-      ga.bias = b_out[g];
+      ga.x = tp.x;
+      ga.w = tp.w;
+      ga.bias = tp.bias;
       ga.y[0] = pa.rows;
-      ga.M = Q.q_end - Q.q_begin;
-      ga.N = t.kp;
-      ga.K = hid;
+      ga.M = tp.M;
+      ga.N = tp.N;
+      ga.K = tp.K;
       ga.split = t.kp;
       ga.ldx = hid;
       ga.ldy = t.kp;
-      ga.fuse = mssa::kFuseUnembed;
-      ga.patch = &pa;
-      if (mssa::tier_fused(ga)) {
-        fused.push_back(ga);
-        continue;
-      }
-      ga.fuse = 0;
       s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
                        "patch de-embedding GEMM launch");
       if (s != MSSA_OK) return s;
       s = check_device(mssa::launch_unpatchify(pa, hs), "unpatchify launch");
       if (s != MSSA_OK) return s;
     }
-    return launch_tiers(fused, "patch de-embedding launch", hs);
+    return launch_tiers(fused, false, "patch de-embedding launch", hs);
   });
 }
 

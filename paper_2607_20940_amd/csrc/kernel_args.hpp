@@ -203,31 +203,26 @@ struct GemmArgs {
   float* partial;     // k_splits > 1: fp32 partial tiles of every K slice (launch_gemm_split)
   int32_t k_splits;   // 0 or 1: the whole K in one block
   float y0_scale;     // factor on the outputs of y[0] (columns < split), applied to the fp32 sum before rounding
-  // MSP tiers in one kernel (tier_fused): the rows of x (embedding) or of the
-  // outputs (de-embedding) are the patches of `patch`, gathered from or
-  // scattered to its latent by the GEMM itself; x or y[0] is then not used.
-  // next: another tier's problem for the same launch (a host pointer).
-  int32_t fuse;       // 0: a plain product; kFuseEmbed, kFuseUnembed
-  const PatchArgs* patch;
-  const GemmArgs* next;
 };
-constexpr int kFuseEmbed = 1, kFuseUnembed = 2;
 
-// The tiers of one fused launch.
+// Tiers whose GEMM gathers its rows from the latent (embedding) or scatters
+// its outputs to it (de-embedding), in one launch (launch_tiers).
 struct TierProblem {
   const void* x;      // de-embedding: tokens [M, K]
-  const void* w;
-  const void* bias;
+  const void* w;      // [N, K]
+  const void* bias;   // [N]
   void* y;            // embedding: tokens [M, N]
-  PatchArgs patch;
+  PatchArgs patch;    // rows not used
   int32_t M, N, K;
-  int32_t block_begin;
-  int32_t tiles_per_block;  // embedding: feature tiles of one block
+  int32_t block_begin;      // (set by tier_blocks)
+  int32_t tiles_per_block;  // embedding: feature tiles of one block (set by tier_blocks)
 };
 struct TierArgs {
   TierProblem g[kMaxGroups];
   int32_t n;
 };
+constexpr int kEmbedTile = 64;    // rows of a block and features of a wave's step of the fused embedding
+constexpr int kEmbedMaxK = 256;   // its longest K
 constexpr int kUnembedTile = 64;  // output tile (rows and features) of the fused de-embedding
 
 struct PoolJobArgs {

@@ -44,12 +44,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 // (Host code in plan.cpp: the rule is part of the static launch plan.)
 int gemm_k_splits(int32_t M, int32_t N, int32_t K);
 int64_t gemm_split_bytes(int32_t M, int32_t N, int32_t K);
-// A fused tier GEMM (a.fuse) runs here too, with its `next` tiers in one launch.
 hipError_t launch_gemm_split(const GemmArgs& a, float* partial, hipStream_t stream);
 
-// May this tier's GEMM (a.fuse, a.patch set) gather or scatter its patches
-// itself?  (Host code in plan.cpp.)
-bool tier_fused(const GemmArgs& a);
+// Tiers whose GEMM moves its own patches.  (Host code in plan.cpp: may this
+// tier be one, and the blocks of a launch of such tiers, whose shares it sets.)
+bool tier_fused(const TierProblem& t, bool embed);
+int64_t tier_blocks(TierArgs& a, bool embed);
+hipError_t launch_tiers(const TierArgs& a, int64_t blocks, bool embed, hipStream_t stream);
 
 // Resident blocks per CU of the bf16 attention kernel (0 if unknown).
 int forward_blocks_per_cu(int head_dim);

@@ -651,14 +651,41 @@ int64_t gemm_split_bytes(int32_t M, int32_t N, int32_t K) {
 // of the 1.3B window).  The de-embedding takes 64 x 64 tiles: while the output
 // is narrow (N <= 256: 46 us -> 18 us for that window) or has so few tiles that
 // a 128 x 128 tile would leave the chip idle.
-bool tier_fused(const GemmArgs& a) {
-  const PatchArgs& p = *a.patch;
+bool tier_fused(const TierProblem& t, bool embed) {
+  const PatchArgs& p = t.patch;
   const bool pairs = p.P % 2 == 0 && p.W % 2 == 0 && (p.frame0 + p.n_frames) * p.C * p.H * p.W <= 0x7fffffff;
   auto at = [](const void* q, uintptr_t n) { return (reinterpret_cast<uintptr_t>(q) & (n - 1)) == 0; };
-  if (!pairs || a.K % kGemmStage != 0) return false;
-  if (a.fuse == kFuseEmbed) return a.K <= 256 && a.N % 8 == 0 && at(a.bias, 8) && at(a.y[0], 16);
-  const int64_t tiles = int64_t{(a.M + kUnembedTile - 1) / kUnembedTile} * ((a.N + kUnembedTile - 1) / kUnembedTile);
-  return (a.N <= 256 || tiles <= 512) && at(a.bias, 2);
+  if (!pairs || t.K % kGemmStage != 0) return false;
+  if (embed) return t.K <= kEmbedMaxK && t.N % 8 == 0 && at(t.bias, 8) && at(t.y, 16);
+  const int64_t tiles = int64_t{ceil_div(t.M, kUnembedTile)} * ceil_div(t.N, kUnembedTile);
+  return (t.N <= 256 || tiles <= 512) && at(t.bias, 2);
+}
+
+int64_t tier_blocks(TierArgs& a, bool embed) {
+  // Embedding: feature steps per block (a multiple of its four waves) so that
+  // at most about 512 blocks, two per CU and so one round, share the work; a
+  // step costs its K stages and its stores (about 1.5 stages).
+  auto step = [](const TierProblem& t) { return t.K / kGemmStage + 1.5; };
+  double work = 0;
+  for (int i = 0; i < a.n; ++i)
+    work += double{1} * ceil_div(a.g[i].M, kEmbedTile) * ceil_div(a.g[i].N, kEmbedTile) * step(a.g[i]);
+  int64_t blocks = 0;
+  for (int i = 0; i < a.n; ++i) {
+    TierProblem& t = a.g[i];
+    t.block_begin = static_cast<int32_t>(blocks);
+    t.tiles_per_block = 1;
+    int64_t cols = ceil_div(t.N, embed ? kEmbedTile : kUnembedTile);
+    if (embed) {
+      const int64_t quads = (cols + 3) / 4;
+      const int64_t most = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(work / 512 / step(t) / 4)));
+      const int64_t chunks = (quads + most - 1) / most;
+      t.tiles_per_block = static_cast<int32_t>(4 * ((quads + chunks - 1) / chunks));
+      cols = (cols + t.tiles_per_block - 1) / t.tiles_per_block;
+    }
+    blocks += ceil_div(t.M, embed ? kEmbedTile : kUnembedTile) * cols;
+    if (blocks > 0x7fffffff) break;
+  }
+  return blocks;
 }
 
 }  // namespace mssa

@@ -24,9 +24,6 @@
 //                      the GEMM, all tiers in one launch (tier_fused).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <cmath>
-
 #include "kernels.hpp"
 #include "lds_stage.hpp"
 
@@ -549,7 +546,7 @@ __device__ inline void feature_of(int k, int P, int& c, int& dy, int& dx) {
 // 1.3B window) and by latency: the same product with W staged in LDS for the
 // block spent its time in barriers and waits (26-31 us for the window's two
 // tiers, whether two or four blocks shared a CU).
-constexpr int kEmbM = 64, kEmbN = 64, kEmbK = 256;  // rows per block, features per wave step, longest K
+constexpr int kEmbM = kEmbedTile, kEmbN = kEmbedTile, kEmbK = kEmbedMaxK;  // rows per block, features per wave step, longest K
 
 __global__ __launch_bounds__(kTierThreads, 2) void embed_kernel(TierArgs a) {
   constexpr int kXs = kEmbM * kG2K * 2;     // bytes of one 64-deep K slice of the rows
@@ -859,58 +856,22 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-namespace {
-
-hipError_t launch_fused(const GemmArgs& a, hipStream_t stream) {
-  TierArgs t{};
-  const bool embed = a.fuse == kFuseEmbed;
-  const int bm = embed ? kEmbM : kUnembedTile, bn = embed ? kEmbN : kUnembedTile;
-  // Embedding: feature steps per block (a multiple of its four waves) so that
-  // at most about 512 blocks, two per CU and so one round, share the work; a
-  // step costs its K stages and its stores (about 1.5 stages).
-  double work = 0;
-  for (const GemmArgs* p = &a; p; p = p->next)
-    work += std::ceil(p->M / double{kEmbM}) * std::ceil(p->N / double{kEmbN}) * (p->K / kG2K + 1.5);
-  int64_t blocks = 0;
-  for (const GemmArgs* p = &a; p; p = p->next) {
-    if (t.n == kMaxGroups || p->fuse != a.fuse || !tier_fused(*p)) return hipErrorInvalidValue;
-    if (p->M <= 0) continue;
-    TierProblem& g = t.g[t.n++];
-    g.x = p->x;
-    g.w = p->w;
-    g.bias = p->bias;
-    g.y = p->y[0];
-    g.patch = *p->patch;
-    g.M = p->M;
-    g.N = p->N;
-    g.K = p->K;
-    g.block_begin = static_cast<int32_t>(blocks);
-    int64_t tiles_n = (p->N + bn - 1) / bn;
-    if (embed) {
-      const int64_t quads = (tiles_n + 3) / 4;
-      const int64_t most = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(work / 512 / (p->K / kG2K + 1.5) / 4)));
-      const int64_t chunks = (quads + most - 1) / most;
-      g.tiles_per_block = static_cast<int32_t>(4 * ((quads + chunks - 1) / chunks));
-      tiles_n = (tiles_n + g.tiles_per_block - 1) / g.tiles_per_block;
-    }
-    blocks += static_cast<int64_t>((p->M + bm - 1) / bm) * tiles_n;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  }
+hipError_t launch_tiers(const TierArgs& a, int64_t blocks, bool embed, hipStream_t stream) {
   if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7fffffff || a.n < 1 || a.n > kMaxGroups) return hipErrorInvalidValue;
+  for (int i = 0; i < a.n; ++i)
+    if (!tier_fused(a.g[i], embed)) return hipErrorInvalidValue;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  if (a.fuse == kFuseEmbed)
-    hipLaunchKernelGGL(embed_kernel, grid, dim3(kTierThreads), 0, stream, t);
+  if (embed)
+    hipLaunchKernelGGL(embed_kernel, grid, dim3(kTierThreads), 0, stream, a);
   else if (blocks <= 256)
-    hipLaunchKernelGGL(unembed_kernel<2>, grid, dim3(2 * kTierThreads), 0, stream, t);
+    hipLaunchKernelGGL(unembed_kernel<2>, grid, dim3(2 * kTierThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(unembed_kernel<1>, grid, dim3(kTierThreads), 0, stream, t);
+    hipLaunchKernelGGL(unembed_kernel<1>, grid, dim3(kTierThreads), 0, stream, a);
   return hipGetLastError();
 }
 
-}  // namespace
-
 hipError_t launch_gemm_split(const GemmArgs& a, float* partial, hipStream_t stream) {
-  if (a.fuse) return launch_fused(a, stream);
   const int s = gemm_k_splits(a.M, a.N, a.K);
   if (s <= 1 || !partial || !dma_epilogue_ok(a)) return launch_gemm(a, stream);
   GemmArgs b = a;

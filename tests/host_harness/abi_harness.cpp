@@ -120,6 +120,7 @@ int forward_blocks_per_cu(int) { return 1; }
 
 // What the last forward and backward launches were given.
 int g_key_splits = 0, g_ranges = 0, g_kv_keys = 0;
+int64_t g_tier_launches = 0, g_split_forwards = 0;
 
 hipError_t launch_pool(const PoolArgs& a, int n_blocks, bool bf16, hipStream_t) {
   const int64_t rb = a.ld * (bf16 ? 2 : 4);
@@ -175,6 +176,16 @@ hipError_t launch_forward(const FwdArgs& a, int head_dim, bool bf16, hipStream_t
     tiles += int64_t{G.n_qtiles} * a.num_heads * t;
   }
   if (blocks != a.n_blocks) failure("forward: n_blocks");
+  // 32-query items (fp32, and bf16 with key_splits > 0): a record per item and
+  // split where a context is split
+  if (a.key_splits < (bf16 ? 0 : 1)) failure("forward: key_splits");
+  if (a.key_splits > 1) {
+    int64_t items = 0;
+    for (int g = 0; g < a.n_groups; ++g)
+      items += ceil_div(a.groups[g].q_end - a.groups[g].q_begin, kFwdF32BM) * a.num_heads;
+    check_range(a.partial, items * a.key_splits * split_record_floats(head_dim) * 4, "forward split records");
+    ++g_split_forwards;
+  }
   if (bf16) {
     if (tiles != a.total_tiles) failure("forward: total_tiles");
     if (a.n_ranges > 1) {
@@ -300,6 +311,37 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t) {
     check_range(a.y[j], (int64_t{a.M} - 1) * a.ldy * 2 + int64_t{a.split} * 2, "gemm y");
   // only the QKV projection (three outputs) may scale its first output
   if (!std::isfinite(a.y0_scale) || (a.split == a.N && a.y0_scale != 1.f)) failure("gemm y0_scale");
+  return hipSuccess;
+}
+
+// Tiers that move their own patches: the latent frames they gather or scatter,
+// what is read and written at the other end, what the kernels take for granted
+// (tier_fused), and the blocks that cover every row and feature once.
+hipError_t launch_tiers(const TierArgs& a, int64_t blocks, bool embed, hipStream_t) {
+  ++g_tier_launches;
+  int64_t want = 0;
+  for (int i = 0; i < a.n; ++i) {
+    const TierProblem& t = a.g[i];
+    const PatchArgs& p = t.patch;
+    check_range(static_cast<char*>(p.latent) + p.frame0 * p.C * p.H * p.W * 2, p.n_frames * p.C * p.H * p.W * 2,
+                embed ? "embedded latent" : "de-embedded latent");
+    if (p.gh != ceil_div(p.H, p.P) || p.gw != ceil_div(p.W, p.P) || int64_t{t.M} != p.n_frames * p.gh * p.gw)
+      failure("tier patch grid");
+    if ((embed ? t.K : t.N) != p.C * p.P * p.P) failure("tier patch features");
+    if (embed)
+      check_range(t.y, int64_t{t.M} * t.N * 2, "embedded tokens");
+    else
+      check_range(t.x, int64_t{t.M} * t.K * 2, "de-embedded tokens");
+    check_range(t.w, int64_t{t.N} * t.K * 2, "tier weights");
+    check_range(t.bias, int64_t{t.N} * 2, "tier bias");
+    if (!tier_fused(t, embed) || t.K % kGemmStage != 0 || p.P % 2 != 0 || p.W % 2 != 0 ||
+        (embed && (t.K > kEmbedMaxK || t.N % 8 != 0)))
+      failure("tier shape");
+    if (t.block_begin != want || t.tiles_per_block < 1 || (embed && t.tiles_per_block % 4 != 0)) failure("tier blocks");
+    want += ceil_div(t.M, embed ? kEmbedTile : kUnembedTile) *
+            ceil_div(ceil_div(t.N, embed ? kEmbedTile : kUnembedTile), t.tiles_per_block);
+  }
+  if (want != blocks || a.n < 1 || a.n > kMaxGroups) failure("tier grid");
   return hipSuccess;
 }
 
@@ -479,7 +521,7 @@ void exercise(const mssa_plan_desc& desc, int32_t attention_blocks) {
     }
   }
   if (desc.dtype == MSSA_BF16) {
-    mssa_tier_desc tier{2, 2, desc.num_heads * desc.head_dim};
+    mssa_tier_desc tier{desc.grid_h % 3 == 0 ? 2 : 16, 2, desc.num_heads * desc.head_dim};
     int64_t tws = 0;
     expect(mssa_tier_workspace_size(plan, &tier, &tws), MSSA_OK, "tier workspace size");
     void* tw = dev_alloc(tws);
@@ -647,6 +689,10 @@ int main(int argc, char** argv) {
              " d=" + std::to_string(d.head_dim) + " dt=" + std::to_string(d.dtype) + " fl=" + std::to_string(flags);
     exercise(d, rnd(3) == 0 ? 1 + static_cast<int>(rnd(600)) : 0);
   }
+  g_case = "coverage";
+  std::printf("%d tier launches, %d forwards with split records\n", static_cast<int>(mssa::g_tier_launches),
+              static_cast<int>(mssa::g_split_forwards));
+  if (mssa::g_tier_launches < 100 || mssa::g_split_forwards < 10) failure("paths that the descriptors reach");
   std::printf("%d checks, %d failures\n", g_checks, g_failures);
   return g_failures == 0 ? 0 : 1;
 }
