@@ -887,6 +887,22 @@ mssa::PatchArgs tier_patch(const TierGroup& t, const mssa_tier_desc* tier, void*
   return pa;
 }
 
+// The product of a tier whose patch rows lie in the workspace.
+mssa::GemmArgs tier_gemm(const mssa::TierProblem& t, bool embed) {
+  mssa::GemmArgs ga{};
+  ga.y0_scale = 1.f;
+  ga.x = embed ? t.patch.rows : t.x;
+  ga.w = t.w;
+  ga.bias = t.bias;
+  ga.y[0] = embed ? t.y : t.patch.rows;
+  ga.M = t.M;
+  ga.N = ga.split = t.N;
+  ga.K = t.K;
+  ga.ldx = t.K;
+  ga.ldy = t.N;
+  return ga;
+}
+
 // The tiers that move their own patches, in one launch.
 mssa_status launch_tiers(mssa::TierArgs& a, bool embed, const char* what, hipStream_t hs) {
   if (a.n == 0) return MSSA_OK;
@@ -923,7 +939,10 @@ mssa_status mssa_patch_embed(mssa_plan plan, const mssa_tier_desc* tier, const v
       if (!w_embed[g] || !b_embed[g] || !aligned16(w_embed[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
+    // the fp32 partial tiles of a split GEMM, used in turn
+    float* const partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + tg.front().partial_off);
     mssa::TierArgs fused{};
+    std::vector<mssa::TierProblem> apart;
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
@@ -937,26 +956,19 @@ mssa_status mssa_patch_embed(mssa_plan plan, const mssa_tier_desc* tier, const v
       tp.M = Q.q_end - Q.q_begin;
       tp.N = hid;
       tp.K = t.kp;
-      if (mssa::tier_fused(tp, true)) {
+      if (mssa::tier_fused(tp, true))
         fused.g[fused.n++] = tp;
-        continue;
-      }
-      mssa::GemmArgs ga{};
-      ga.y0_scale = 1.f;
-      ga.x = pa.rows;
-      ga.w = tp.w;
-      ga.bias = tp.bias;
-      ga.y[0] = tp.y;
-      ga.M = tp.M;
-      ga.N = tp.N;
-      ga.K = tp.K;
-      ga.split = hid;
-      ga.ldx = t.kp;
-      ga.ldy = hid;
-      s = check_device(mssa::launch_patchify(pa, hs), "patchify launch");
+      else
+        apart.push_back(tp);
+    }
+    if (!mssa::tiers_pay(fused, true)) {
+      apart.insert(apart.end(), fused.g, fused.g + fused.n);
+      fused.n = 0;
+    }
+    for (const mssa::TierProblem& tp : apart) {
+      s = check_device(mssa::launch_patchify(tp.patch, hs), "patchify launch");
       if (s != MSSA_OK) return s;
-      s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
-                       "patch embedding GEMM launch");
+      s = check_device(mssa::launch_gemm_split(tier_gemm(tp, true), partial, hs), "patch embedding GEMM launch");
       if (s != MSSA_OK) return s;
     }
     return launch_tiers(fused, true, "patch embedding launch", hs);
@@ -981,7 +993,10 @@ mssa_status mssa_patch_unembed(mssa_plan plan, const mssa_tier_desc* tier, const
       if (!w_out[g] || !b_out[g] || !aligned16(w_out[g])) return fail(MSSA_ERR_INVALID_ARG, "null or misaligned tier weights");
     auto hs = static_cast<hipStream_t>(stream);
     const int32_t H = p.desc.grid_h * tier->patch, W = p.desc.grid_w * tier->patch, hid = tier->hidden;
+    // the fp32 partial tiles of a split GEMM, used in turn
+    float* const partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + tg.front().partial_off);
     mssa::TierArgs fused{};
+    std::vector<mssa::TierProblem> apart;
     for (size_t g = 0; g < tg.size(); ++g) {
       const TierGroup& t = tg[g];
       const mssa::QGroup& Q = p.groups[g];
@@ -994,26 +1009,19 @@ mssa_status mssa_patch_unembed(mssa_plan plan, const mssa_tier_desc* tier, const
       tp.M = Q.q_end - Q.q_begin;
       tp.N = t.kp;
       tp.K = hid;
-      if (mssa::tier_fused(tp, false)) {
+      if (mssa::tier_fused(tp, false))
         fused.g[fused.n++] = tp;
-        continue;
-      }
-      mssa::GemmArgs ga{};
-      ga.y0_scale = 1.f;
-      ga.x = tp.x;
-      ga.w = tp.w;
-      ga.bias = tp.bias;
-      ga.y[0] = pa.rows;
-      ga.M = tp.M;
-      ga.N = tp.N;
-      ga.K = tp.K;
-      ga.split = t.kp;
-      ga.ldx = hid;
-      ga.ldy = t.kp;
-      s = check_device(mssa::launch_gemm_split(ga, reinterpret_cast<float*>(static_cast<char*>(workspace) + t.partial_off), hs),
-                       "patch de-embedding GEMM launch");
+      else
+        apart.push_back(tp);
+    }
+    if (!mssa::tiers_pay(fused, false)) {
+      apart.insert(apart.end(), fused.g, fused.g + fused.n);
+      fused.n = 0;
+    }
+    for (const mssa::TierProblem& tp : apart) {
+      s = check_device(mssa::launch_gemm_split(tier_gemm(tp, false), partial, hs), "patch de-embedding GEMM launch");
       if (s != MSSA_OK) return s;
-      s = check_device(mssa::launch_unpatchify(pa, hs), "unpatchify launch");
+      s = check_device(mssa::launch_unpatchify(tp.patch, hs), "unpatchify launch");
       if (s != MSSA_OK) return s;
     }
     return launch_tiers(fused, false, "patch de-embedding launch", hs);

@@ -47,8 +47,10 @@ int64_t gemm_split_bytes(int32_t M, int32_t N, int32_t K);
 hipError_t launch_gemm_split(const GemmArgs& a, float* partial, hipStream_t stream);
 
 // Tiers whose GEMM moves its own patches.  (Host code in plan.cpp: may this
-// tier be one, and the blocks of a launch of such tiers, whose shares it sets.)
+// tier be one, is one launch of these tiers faster than their separate passes,
+// and the blocks of such a launch, whose shares it sets.)
 bool tier_fused(const TierProblem& t, bool embed);
+bool tiers_pay(const TierArgs& a, bool embed);
 int64_t tier_blocks(TierArgs& a, bool embed);
 hipError_t launch_tiers(const TierArgs& a, int64_t blocks, bool embed, hipStream_t stream);
 

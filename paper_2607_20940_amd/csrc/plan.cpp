@@ -647,10 +647,9 @@ int64_t gemm_split_bytes(int32_t M, int32_t N, int32_t K) {
 
 // Fused tiers move pixels in pairs (even patch rows on an even frame width) and
 // take K in whole 64-element stages with 16-byte rows.  The embedding holds a
-// block's patch rows in LDS, K <= 256 of them (36 us -> 22 us for the two tiers
-// of the 1.3B window).  The de-embedding takes 64 x 64 tiles: while the output
-// is narrow (N <= 256: 46 us -> 18 us for that window) or has so few tiles that
-// a 128 x 128 tile would leave the chip idle.
+// block's patch rows in LDS, K <= 256 of them.  The de-embedding takes 64 x 64
+// tiles: while the output is narrow (N <= 256) or has so few tiles that a
+// 128 x 128 tile would leave the chip idle.
 bool tier_fused(const TierProblem& t, bool embed) {
   const PatchArgs& p = t.patch;
   const bool pairs = p.P % 2 == 0 && p.W % 2 == 0 && (p.frame0 + p.n_frames) * p.C * p.H * p.W <= 0x7fffffff;
@@ -661,31 +660,86 @@ bool tier_fused(const TierProblem& t, bool embed) {
   return (t.N <= 256 || tiles <= 512) && at(t.bias, 2);
 }
 
-int64_t tier_blocks(TierArgs& a, bool embed) {
-  // Embedding: feature steps per block (a multiple of its four waves) so that
-  // at most about 512 blocks, two per CU and so one round, share the work; a
-  // step costs its K stages and its stores (about 1.5 stages).
-  auto step = [](const TierProblem& t) { return t.K / kGemmStage + 1.5; };
-  double work = 0;
-  for (int i = 0; i < a.n; ++i)
-    work += double{1} * ceil_div(a.g[i].M, kEmbedTile) * ceil_div(a.g[i].N, kEmbedTile) * step(a.g[i]);
-  int64_t blocks = 0;
-  for (int i = 0; i < a.n; ++i) {
-    TierProblem& t = a.g[i];
-    t.block_begin = static_cast<int32_t>(blocks);
-    t.tiles_per_block = 1;
-    int64_t cols = ceil_div(t.N, embed ? kEmbedTile : kUnembedTile);
-    if (embed) {
-      const int64_t quads = (cols + 3) / 4;
-      const int64_t most = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(work / 512 / step(t) / 4)));
-      const int64_t chunks = (quads + most - 1) / most;
-      t.tiles_per_block = static_cast<int32_t>(4 * ((quads + chunks - 1) / chunks));
-      cols = (cols + t.tiles_per_block - 1) / t.tiles_per_block;
-    }
-    blocks += ceil_div(t.M, embed ? kEmbedTile : kUnembedTile) * cols;
-    if (blocks > 0x7fffffff) break;
+// One launch for all these tiers, or patches and GEMM tier by tier?  Measured on
+// an MI355X over 660 (embedding) and 430 (de-embedding) random sets of tiers of 8
+// to 48 channels and hidden sizes of 384 to 6400, each both ways.
+// Embedding: the separate passes cost two launches a tier and read the patches
+// twice, but their 256 x 256 tiles read W less often.  Several tiers: one launch
+// up to 1.2e8 output elements (9.3e7 + 2.4e7 in hidden 4928 93.7 -> 75.9 us, but
+// 1.1e8 + 2.8e7 in 4352 136.5 -> 147.6).  A lone tier: always for K = 64; K = 128
+// up to 4e7 (3.7e7 38.0 -> 30.2, 5.8e7 50.4 -> 50.9), 192 up to 2e7 (1.9e7 31.2 ->
+// 27.8, 4.4e7 47.0 -> 56.9), 256 up to 3.5e6 (3.1e6 12.2 -> 10.7, 4.6e6 13.1 ->
+// 15.5).  370 other sets: 0.84 of the separate passes' time on average, 1.15 at
+// worst (lone tiers of K = 128 and 192 scatter by a tenth either way).
+// De-embedding: the separate passes may split a long K over the chip, the fused
+// kernel walks it.  The better one by fitted times (0.2 % above the better one on
+// average, 5 % slower than the separate passes at worst): one tier of 210 tokens
+// on hidden 4928 13.9 us apart and 20.6 in one launch, of 396 tokens and 128
+// features on 5632 17.3 and 23.1, the two tiers of the 1.3B window 46 and 20.
+bool tiers_pay(const TierArgs& a, bool embed) {
+  if (embed) {
+    double outputs = 0;
+    for (int i = 0; i < a.n; ++i) outputs += static_cast<double>(a.g[i].M) * a.g[i].N;
+    if (a.n != 1) return a.n > 1 && outputs <= 1.2e8;
+    const int32_t k = a.g[0].K;
+    return k <= 64 || outputs <= (k <= 128 ? 4e7 : k <= 192 ? 2e7 : 3.5e6);
   }
-  return blocks;
+  double apart = 0, together = 5.88, walked = 0;
+  int64_t tiles = 0, stages = 0;
+  for (int i = 0; i < a.n; ++i) {
+    const TierProblem& t = a.g[i];
+    const double m = t.M, n = t.N, k = t.K, st = k / kGemmStage;
+    const int64_t t128 = int64_t{ceil_div(t.M, kGemmTile)} * ceil_div(t.N, kGemmTile);
+    const int splits = gemm_k_splits(t.M, t.N, t.K);
+    apart += 6.22 + 1e-6 * (5.4 * m * n + 0.13 * m * k + 0.56 * n * k);
+    if (splits > 1)  // a third launch, a slice's stages, the partial tiles
+      apart += 2.92 + 0.435 * st / splits + 0.25e-6 * 4 * splits * static_cast<double>(t128) * kGemmTile * kGemmTile;
+    else
+      apart += 0.548 * st * std::max(1.0, static_cast<double>(t128) / 512);
+    const int64_t cols = ceil_div(t.N, kUnembedTile);
+    tiles += ceil_div(t.M, kUnembedTile) * cols;
+    stages = std::max<int64_t>(stages, t.K / kGemmStage);
+    together += 1e-6 * (0.80 * m * n + 0.038 * m * k);
+    walked += 0.125e-6 * m * k * static_cast<double>(cols);  // the tokens once per 64 features
+  }
+  const double chain = static_cast<double>(stages);
+  together += tiles <= 256 ? 0.189 * chain : 0.27 * chain * static_cast<double>((tiles + 511) / 512) + walked;
+  return together < apart;
+}
+
+int64_t tier_blocks(TierArgs& a, bool embed) {
+  const int bm = embed ? kEmbedTile : kUnembedTile;
+  // Embedding: quads of feature steps (one for each of a block's four waves)
+  // per block so that at most 512 blocks, two per CU and so one round, share
+  // the work; a step costs its K stages and its stores (about 1.5 stages).
+  // Rounding up tier by tier may leave more blocks than that, and the long ones
+  // of the last tier in a second round: the shares of several tiers grow until
+  // they fit, or a block has a whole row of steps (14508 tokens of 64 pixels and
+  // 3720 of 256 in hidden 1664: 631 blocks; such pairs 12 % faster on average).
+  auto step = [](const TierProblem& t) { return t.K / kGemmStage + 1.5; };
+  double share = 0;
+  for (int i = 0; i < a.n; ++i)
+    share += 1.0 * ceil_div(a.g[i].M, bm) * ceil_div(a.g[i].N, bm) * step(a.g[i]) / 512;
+  for (;; share *= 1.125) {
+    int64_t blocks = 0;
+    bool whole_rows = true;
+    for (int i = 0; i < a.n; ++i) {
+      TierProblem& t = a.g[i];
+      t.block_begin = static_cast<int32_t>(std::min<int64_t>(blocks, 0x7fffffff));
+      t.tiles_per_block = 1;
+      int64_t cols = ceil_div(t.N, bm);
+      if (embed) {
+        const int64_t quads = (cols + 3) / 4;
+        const int64_t most = std::max<int64_t>(1, static_cast<int64_t>(std::ceil(share / step(t) / 4)));
+        const int64_t chunks = (quads + most - 1) / most;
+        t.tiles_per_block = static_cast<int32_t>(4 * ((quads + chunks - 1) / chunks));
+        cols = (cols + t.tiles_per_block - 1) / t.tiles_per_block;
+        whole_rows = whole_rows && chunks == 1;
+      }
+      blocks += ceil_div(t.M, bm) * cols;
+    }
+    if (!embed || a.n < 2 || blocks <= 512 || whole_rows) return blocks;
+  }
 }
 
 }  // namespace mssa
