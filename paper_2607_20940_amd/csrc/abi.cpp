@@ -766,7 +766,7 @@ mssa_status mssa_backward(mssa_plan plan, const void* q_win, const void* k_sink,
       A.n_kblocks = static_cast<int32_t>((Q.n_kv + kb - 1) / kb);
     }
     // bf16: heads in chunks of bwd_ds_heads, each chunk's dK/dV kernel
-    // writing the dS tiles its dQ kernel reads; fp32: one launch of each.
+    // writing the dS tiles its dQ kernel reads; fp32: both in one launch.
     const int chunk = bf16 ? p.bwd_ds_heads : nh;
     for (int h0 = 0; h0 < nh; h0 += chunk) {
       a.head0 = h0;

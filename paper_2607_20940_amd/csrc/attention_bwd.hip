@@ -40,6 +40,7 @@
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
+#include "xcd.hpp"
 
 namespace mssa {
 namespace {
@@ -49,16 +50,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
-// Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous eighth of a group's n blocks so that its L2 serves few heads.  Per
-// group, not over the whole grid: the groups' blocks differ in length (293 and
-// 110 steps of the dK/dV kernel on the 1.3B layer), and contiguous eighths of
-// the grid left the XCDs with the short group idle for 30 % of the kernel.
-__device__ inline int xcd_remap(int b, int n) {
-  const int q = n / 8, r = n % 8, x = b % 8, j = b / 8;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
 
 // Context token j of group G -> its K (or V) row, head 0; nullptr past the end.
 template <typename T>
@@ -508,6 +499,9 @@ void dkdv_kernel(BwdArgs a) {
   int g = 0;
   while (g + 1 < a.n_groups && b >= a.groups[g + 1].kv_block_begin) ++g;
   const BwdGroupArgs& G = a.groups[g];
+  // an eighth of every group per XCD, not of the grid: the groups' blocks differ
+  // in length (293 and 110 stages on the 1.3B layer), and contiguous eighths of
+  // the grid left the XCDs with the short group idle for 30 % of the kernel
   const int idx = xcd_remap(b - G.kv_block_begin, G.n_kblocks * a.num_heads);
   const int hl = idx / G.n_kblocks, kt = idx % G.n_kblocks;  // head of the launch
   const int head = a.head0 + hl;

@@ -26,6 +26,7 @@
 
 #include "kernels.hpp"
 #include "split_merge.hpp"
+#include "xcd.hpp"
 
 namespace mssa {
 namespace {
@@ -69,7 +70,8 @@ __device__ inline __amdgpu_buffer_rsrc_t tile_buffer(const float* p, int64_t ld,
 // batches in registers: the next one is in flight during the 16 MFMAs (1024
 // cycles) of the current one.  prefetch() starts the first batch; the caller
 // places it before the work that precedes the product.  Whole tiles in
-// registers (64 + 64 beside the accumulators) spilled.
+// registers (64 + 64 beside the accumulators) spilled; like this the backward
+// for head_dim 128 alone does, five registers.
 constexpr int kBatch = 4;
 
 // A operand of a row product: lane's row l % 32, 16 bytes at 8 j + 4 hh.
@@ -177,13 +179,6 @@ __device__ inline void acc_to_lds(float* dst, const f32x16 (&acc)[D / 32], int n
     for (int db = 0; db < D / 32; ++db) v[db] = acc[db][e];
     *reinterpret_cast<vec*>(dst + (acc_row(e, hh) * 32 + n) * (D / 32)) = v;
   }
-}
-
-// Block -> (group, head, 32-row tile, split).  Blocks are dispatched
-// round-robin over the 8 XCDs; each gets a contiguous eighth.
-__device__ inline int xcd_remap(int b, int n) {
-  const int q = n / 8, r = n % 8, x = b % 8, j = b / 8;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
 }
 
 // ------------------------------------------------------------------ forward

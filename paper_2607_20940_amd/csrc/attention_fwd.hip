@@ -35,6 +35,7 @@
 
 #include "kernels.hpp"
 #include "lds_stage.hpp"
+#include "xcd.hpp"
 
 namespace mssa {
 namespace {
@@ -91,13 +92,6 @@ __device__ inline int64_t range_begin(const FwdArgs& a, int rho) {
   for (int r = 0; r < a.dp_rounds; ++r)
     dp += item_tile(a, static_cast<int64_t>(r) * B + rho) - item_tile(a, static_cast<int64_t>(r) * B);
   return a.tail_begin + static_cast<int64_t>(rho) * a.total_tiles / B - dp;
-}
-
-// Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous eighth of the range indices so that its L2 serves few heads.
-__device__ inline int range_of_block(int b, int B) {
-  const int q = B / 8, r = B % 8, x = b % 8, j = b / 8;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
 }
 
 struct Loc {
@@ -590,7 +584,7 @@ void fwd_bf16_kernel(FwdArgs a) {
   using P = FwdTile<D>;
   // [K buf0 | K buf1 | V buf0 | V buf1], 64 rows of 256 bytes each
   __shared__ __attribute__((aligned(16))) char lds[P::LDS_BYTES];
-  const int rho = range_of_block(blockIdx.x, a.n_ranges);
+  const int rho = xcd_remap(blockIdx.x, a.n_ranges);
   const int64_t S = range_begin(a, rho), E = range_begin(a, rho + 1);
   // The merge of split items reads the tail ranges from this table.
   if (a.range_table && threadIdx.x == 0) {

@@ -21,6 +21,7 @@
 #include "kernels.hpp"
 #include "lds_stage.hpp"
 #include "split_merge.hpp"
+#include "xcd.hpp"
 
 namespace mssa {
 namespace {
@@ -42,11 +43,6 @@ __device__ inline void wait_transfers() {
 
 // This wave's LDS reads have returned: their tile may be overwritten.
 __device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-__device__ inline int xcd_remap(int b, int n) {
-  const int q = n / 8, r = n % 8, x = b % 8, j = b / 8;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + j;
-}
 
 template <int D>
 __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))

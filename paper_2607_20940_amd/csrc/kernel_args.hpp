@@ -25,6 +25,10 @@ constexpr int kSplitThreads = 64 * kSplitWaves;
 
 constexpr int kPoolThreads = 256;
 
+// Byte offset past any buffer range the kernels build: a transfer lane pointed
+// here writes zeros, a store is dropped (no 32-bit wrap of offset + 16).
+constexpr uint32_t kPastEnd = 0x7ffffff0u;
+
 struct FwdRunArgs {
   const void* k;   // first token of the run (head 0, channel 0)
   const void* v;

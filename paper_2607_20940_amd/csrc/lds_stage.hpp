@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "kernel_args.hpp"
+
 namespace mssa {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -107,10 +109,6 @@ __device__ inline i32x4 rsrc_of(const void* base, uint32_t bytes) {
   r[3] = 0x00020000;
   return r;
 }
-
-// Byte offset past any buffer this library builds: a transfer lane pointed
-// here writes zeros (no 32-bit wrap of offset + 16).
-constexpr uint32_t kPastEnd = 0x7ffffff0u;
 
 // Value of lane l ^ 32.  v_permlane32_swap exchanges the upper half of its
 // first operand with the lower half of its second; whether the compiler gives
