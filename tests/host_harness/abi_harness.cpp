@@ -521,7 +521,7 @@ void exercise(const mssa_plan_desc& desc, int32_t attention_blocks) {
     }
   }
   if (desc.dtype == MSSA_BF16) {
-    mssa_tier_desc tier{desc.grid_h % 3 == 0 ? 2 : 16, 2, desc.num_heads * desc.head_dim};
+    mssa_tier_desc tier{desc.grid_h % 5 == 1 ? 2 : 16, 2, desc.num_heads * desc.head_dim};
     int64_t tws = 0;
     expect(mssa_tier_workspace_size(plan, &tier, &tws), MSSA_OK, "tier workspace size");
     void* tw = dev_alloc(tws);
@@ -635,15 +635,25 @@ int main(int argc, char** argv) {
   }
   // The kernels that tests of their own are there for are the ones the plans of
   // those tests take on 256 CUs: 32-query items (blocks per item; 0: persistent
-  // kernel) and keys per dK/dV block.
-  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1};
+  // kernel), keys per dK/dV block, launches of tiers that move their own patches
+  // (embedding and de-embedding, hidden size: all the heads' channels), tile
+  // ranges; -1: not looked at.
+  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1}, s2[1] = {2};
   const struct {
     const char* what;
     mssa_plan_desc d;
-    int splits, keys;
+    int splits, keys, tiers = -1, ranges = -1;
   } chosen[] = {
       {"preview layer", make_desc(5, s12, 10, 13, 3, 1, 2, 2, 128, MSSA_BF16, 0), 1, 128},
-      {"1.3B layer", named[1].second, 0, 256},
+      {"1.3B layer", named[1].second, 0, 256, 2},
+      {"half-resolution stream", make_desc(5, s12, 15, 26, 3, 3, 12, 4, 128, MSSA_BF16, MSSA_PLAN_POOLED_HIST_RING), 0,
+       -1, -1, 256},
+      {"small layers: two blocks, 64", make_desc(2, t12, 20, 23, 1, 1, 8, 6, 64, MSSA_BF16, 0), 2, -1},
+      {"small layers: two blocks, 128", make_desc(2, t12, 20, 23, 1, 1, 8, 6, 128, MSSA_BF16, 0), 2, -1},
+      {"small layers: eight blocks, 64", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 64, MSSA_BF16, 0), 8, -1},
+      {"small layers: eight blocks, 128", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 128, MSSA_BF16, 0), 8, -1},
+      {"one tier, long hidden", make_desc(1, s11, 14, 15, 1, 0, 0, 77, 64, MSSA_BF16, 0), -1, -1, 1},
+      {"one tier, wide embedding", make_desc(1, s2, 52, 60, 1, 0, 0, 81, 64, MSSA_BF16, 0), -1, -1, 0},
       {"key blocks: one coarse stage, 64", make_desc(3, s114, 16, 24, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
       {"key blocks: one coarse stage, 128", make_desc(3, s114, 16, 24, 1, 0, 1, 256, 128, MSSA_BF16, 0), -1, 256},
       {"key blocks: two coarse stages, 64", make_desc(3, s114, 23, 34, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
@@ -659,10 +669,13 @@ int main(int argc, char** argv) {
   };
   for (const auto& c : chosen) {
     g_case = c.what;
+    const int64_t before = mssa::g_tier_launches;
     exercise(c.d, 0);
     if (c.splits >= 0 && mssa::g_key_splits != c.splits) failure("forward kernel chosen");
-    if (mssa::g_kv_keys != c.keys) failure("keys per dK/dV block chosen");
-    g_checks += 2;
+    if (c.keys >= 0 && mssa::g_kv_keys != c.keys) failure("keys per dK/dV block chosen");
+    if (c.tiers >= 0 && mssa::g_tier_launches - before != c.tiers) failure("tiers in one launch");
+    if (c.ranges >= 0 && mssa::g_ranges != c.ranges) failure("tile ranges chosen");
+    g_checks += 4;
   }
   g_case = "1.3B layer, 7 attention blocks";
   exercise(named[1].second, 7);

@@ -130,9 +130,9 @@ def _assert_grads(got, ref, dtype, label, heads=None):
     return res
 
 
-def _check(desc, dtype, seed, amp, label, gamp=1.0):
+def _check(desc, dtype, seed, amp, label, gamp=1.0, attention_blocks=0):
     print(f"[bwd] {label} desc={desc} dtype={dtype} seed={seed}", flush=True)
-    r = BwdRun(desc, dtype, seed, amp, gamp)
+    r = BwdRun(desc, dtype, seed, amp, gamp, attention_blocks=attention_blocks)
     got = r.run()
     res = _assert_grads(r.grads(), r.oracle(), dtype, label)
     lse = r.lse.cpu().numpy().astype(np.float64).reshape(desc["num_heads"], -1)

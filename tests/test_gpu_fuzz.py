@@ -88,3 +88,42 @@ def test_forward_random_descriptor_q_prescaled(case):
 def test_backward_random_descriptor_q_prescaled(case):
     i, desc, dtype, seed = case
     bwd_check(dict(desc, q_prescaled=True), dtype, seed, 1.0, f"fuzz pre-scaled {_id(case)}")
+
+
+# The same descriptors on the persistent kernel, which by itself a plan takes for
+# larger layers: 1, 5 or 64 tile ranges, so that items are whole, cut into a few
+# pieces and into many.
+def _blocks(i):
+    return (1, 5, 64)[i % 3]
+
+
+BF16 = [c for c in FWD_CASES if c[2] == "bf16"]
+BWD_BF16 = [c for c in BWD_CASES if c[2] == "bf16"]
+
+
+@pytest.mark.parametrize("case", BF16, ids=_id)
+def test_forward_random_descriptor_on_given_blocks(case):
+    i, desc, dtype, seed = case
+    print(f"[fuzz] forward {_blocks(i)} blocks {_id(case)} desc={desc} seed={seed}", flush=True)
+    r = GpuRun(desc, dtype, seed, 1.0 / np.sqrt(128.0), attention_blocks=_blocks(i))
+    r.run()
+    assert_close(r.output(), r.oracle(), dtype, _id(case))
+
+
+@pytest.mark.parametrize("case", QPRE_FWD_CASES, ids=_id)
+def test_forward_random_descriptor_q_prescaled_on_given_blocks(case):
+    i, desc, _, seed = case
+    desc = dict(desc, q_prescaled=True)
+    print(f"[fuzz] forward pre-scaled {_blocks(i)} blocks {_id(case)} desc={desc} seed={seed}", flush=True)
+    r = GpuRun(desc, "bf16", seed, 1.0, attention_blocks=_blocks(i))
+    r.run()
+    assert_close(r.output(), r.oracle(), "bf16", _id(case))
+
+
+@pytest.mark.parametrize("prescaled", [False, True])
+@pytest.mark.parametrize("case", BWD_BF16, ids=_id)
+def test_backward_random_descriptor_on_given_blocks(case, prescaled):
+    """Its log-sum-exp, and the gradients made from it."""
+    i, desc, dtype, seed = case
+    bwd_check(dict(desc, q_prescaled=prescaled), dtype, seed, 1.0 if prescaled else 1.0 / np.sqrt(128.0),
+              f"fuzz {_blocks(i)} blocks {_id(case)}", attention_blocks=_blocks(i))

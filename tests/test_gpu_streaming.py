@@ -134,6 +134,20 @@ SMALL = dict(STREAMING, layer=dict(num_states=3, scales=[1, 1, 2], grid_h=6, gri
              hist_start_frames=2, hist_cap_frames=6, seed_base=40, init_seed_base=7000)
 
 
+@pytest.mark.parametrize("kw", [{}, dict(pooled_ring=True), dict(head_in_ring=True, q_prescaled=True)],
+                         ids=["copied", "pooled_ring", "head_in_ring"])
+def test_streaming_fewer_items_than_cus_sampled(kw):
+    """Half the resolution of the streaming workload, 4 heads: 56 items whose
+    contexts a plan cuts into a range per CU; sampled rows and heads once the
+    ring has wrapped around."""
+    layer = dict(STREAMING["layer"], grid_h=15, grid_w=26, num_heads=4)
+    w = dict(STREAMING, layer=layer, hist_start_frames=9, hist_cap_frames=12)
+    n_q = 6 * 390 + 9 * 8 * 13
+    rows = np.unique(np.concatenate([[0, 255, 256, 2339, 2340, n_q - 1], np.random.default_rng(1).integers(0, n_q, 60)]))
+    st, n = _run(w, layers=1, passes=4, check=lambda p, L: (rows, [0, 3]) if p in (0, 3) else None, **kw)
+    assert n == 2
+
+
 def test_streaming_pooled_ring_small_every_output():
     """The pooled-history-ring path against the oracle: every output of two
     small layers through the ring's fill and wrap-arounds."""

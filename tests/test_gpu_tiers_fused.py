@@ -3,8 +3,9 @@ their tiles and of the rule that chooses them: one token, tokens and features
 one past a 64-tile, an odd number of K stages (the two halves of the
 de-embedding's block), more tiles than CUs, K = 64 .. 256 and 1024 for the
 embedding, and sizes that stay with the separate passes (odd patches, odd frame
-widths, hidden sizes that are no multiple of 64).  Outputs against the fp64
-oracle with the tolerance of test_gpu_tiers."""
+widths, hidden sizes that are no multiple of 64, a de-embedding of few tokens on
+a long hidden size, a wide embedding).  Outputs against the fp64 oracle with the
+tolerance of test_gpu_tiers."""
 
 import numpy as np
 import pytest
@@ -29,6 +30,8 @@ CASES = {
     "odd_patch": ([1, 2], 5, 7, 1, 16, 1, 128),
     "odd_channels_patch_3": ([1, 2], 4, 5, 1, 8, 3, 64),
     "hidden_past_a_tile": ([1], 3, 5, 2, 16, 2, 200),
+    "one_tier_long_hidden": ([1], 14, 15, 1, 16, 2, 4928),
+    "one_tier_wide_embedding": ([2], 52, 60, 1, 16, 2, 5184),
 }
 
 
