@@ -148,12 +148,12 @@ mssa_status mssa_plan_create(const mssa_plan_desc* desc, mssa_plan* out);
  * head and 256-query tile, each a sequence of 64-key tiles) is cut into
  * attention_blocks equal shares, one per block; a share may end inside an
  * item, whose pieces are then merged in a fixed order.  attention_blocks ==
- * 0 takes one block per resident slot of the current device (512 without a
- * device), as mssa_plan_create does, or for small layers a schedule of
- * 32-query blocks; fewer blocks leave compute units to other streams, more
- * run in several waves.  The plan's workspace size depends on
- * it.  MSSA_ERR_INVALID_ARG for attention_blocks < 0; otherwise as
- * mssa_plan_create. */
+ * 0 leaves the schedule to the library, as mssa_plan_create does: one block
+ * per resident slot of the current device (512 without a device), for small
+ * layers one per item or a schedule of 32-query blocks where that is faster.
+ * Fewer blocks leave compute units to other streams, more run in several
+ * waves.  The plan's workspace size depends on it.  MSSA_ERR_INVALID_ARG for
+ * attention_blocks < 0; otherwise as mssa_plan_create. */
 mssa_status mssa_plan_create_ex(const mssa_plan_desc* desc, int32_t attention_blocks, mssa_plan* out);
 
 /* Release a plan (NULL is ignored).  The caller must not use it afterwards

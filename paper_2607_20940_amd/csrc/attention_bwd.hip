@@ -132,7 +132,7 @@ __device__ inline int swz(int row, int col) { return swz256(row, col); }
 // them.  A block's chain of stages is bound by their latency (about 0.85 us
 // each), so where the blocks leave CUs idle the context is split over
 // dq_splits of them (6 heads of 64 on 17 x 23: 36 blocks, 45 us; with 7 splits
-// 15 us and 5 us for the sum).  A split's sum (fp32) takes the place of the dS
+// 14 us and 6 us for the sum).  A split's sum (fp32) takes the place of the dS
 // tiles its wave has read, which no one else reads: D / 32 tiles' bytes, so a
 // split has at least as many stages (dq_splits of its group, 1: no split).
 template <int D>
@@ -468,11 +468,12 @@ __device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c
 // pre-scaled: c = 1) and dP as dP - rowsum.  dS (bf16, the value the dK product
 // uses) goes to its tile in HBM by range-checked stores at a per-lane offset
 // fixed for the whole kernel.
-// Measured (12 heads of 128, 9360 + 3510 queries on 26910 and 12870 keys): 3.25 -
-// 3.4 ms, matrix cores busy 75 % of the cycles a wave is there, the clock set
-// by power; pairs of waves sharing a SIMD, one on the matrix core and one on
-// the softmax, handing P over through LDS behind two barriers per 64 queries:
-// 4.24 - 4.43 ms, 42 %, 6.8 instructions per MFMA beside it where this has 4.1.
+// Measured (12 heads of 128, 9360 + 3510 queries on 26910 and 12870 keys, KB = 2):
+// 2.96 - 3.2 ms, matrix cores busy 70 % of the cycles (a wave is there 91 % of
+// them: the grid's end), LDS 31 %, the clock (1.6 GHz) set by power; pairs of
+// waves sharing a SIMD, one on the matrix core and one on the softmax, handing P
+// over through LDS behind two barriers per 64 queries: 4.24 - 4.43 ms, 44 %.
+// Vector, scalar and LDS instructions per MFMA: 3.5, with the pairs 6.8.
 // Whole backward of small layers with those pairs of waves, KB = 2 and KB = 1: 13
 // heads of 128, 108 queries on 489 keys and two coarser groups 40.1, 53.3 and
 // 41.3 us; 3 heads of 64, 1275 on 5341 and two groups 114, 80.3 and 66.8.
