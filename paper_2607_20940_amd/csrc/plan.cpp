@@ -107,6 +107,14 @@ struct FwdChoice {
 // - Persistent kernel, whole items, no records and no merge, where the items
 //   are equally long and no more than the CUs: u0 and, per tile, u1 + u2 items
 //   (the clock falls as CUs fill).
+// - A merge is one more launch, 3.4 us of the host, and below some length a
+//   program that launches pass by pass (here through the Python binding) is bound
+//   by the host: a merging schedule counts as no shorter than `host` + 3.4 (the
+//   shorter of two such on the device is taken).  That leaves out splits that save
+//   less than the launch costs (3 heads of 64, 588 queries on 2352 keys, streamed:
+//   16.3 us a layer, 18.9 split in four).  Of 148 small layers launched so the
+//   choice is 0.2 % (passes) and 0.4 % (streamed) above the best split on average,
+//   15 % and 11 % at worst; without this 1.4, 3.7, 17 and 20 %.
 // A schedule has to be better than those before it by 3 %.
 // Measured, small S = 1, 2, 4 / one range per CU / whole items: 2 heads of 128
 // on 270 queries and 4372 keys (and fewer at 2x and 4x) 23.8, 19.7, 16.4 /
@@ -124,6 +132,8 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
   const Fit f = p.desc.head_dim == 128
                     ? Fit{2.1, 4.6, 1.04, 0.25, 3.1, 0.59, 14.0, 12.6, 1.745, 0.44, 15.0, 0.96, 0.0023}
                     : Fit{2.6, 3.25, 0.89, 0.08, 2.3, 0.46, 9.6, 10.6, 1.14, 0.40, 11.7, 0.91, 0.0005};
+  constexpr double kLaunch = 3.4;
+  const double host = p.head_ring ? 15.0 : p.hist_ring ? 20.0 : 12.5;
   const double n_cus = static_cast<double>(cus);
   const int32_t longest = *std::max_element(sc.tiles_per_item.begin(), sc.tiles_per_item.end());
   const bool equal = *std::min_element(sc.tiles_per_item.begin(), sc.tiles_per_item.end()) == longest;
@@ -131,12 +141,13 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
   if (!fits(range_records(p, std::min(best.ranges, sc.total_tiles)))) best.ranges = std::min<int64_t>(cus, n_items);
   const double ranges = static_cast<double>(std::max<int64_t>(1, std::min(best.ranges, sc.total_tiles)));
   const double share = std::max(1.0, static_cast<double>(sc.total_tiles) / ranges);  // tiles of a range
-  double t_best = f.p0 + f.pr * ranges / n_cus + f.p1 * share + f.p2 * longest / share;
+  double on_device = f.p0 + f.pr * ranges / n_cus + f.p1 * share + f.p2 * longest / share;
+  double t_best = std::max(on_device, host + kLaunch);
   if (equal && n_items <= cus) {
     const double t = f.u0 + longest * (f.u1 + f.u2 * static_cast<double>(n_items));
     if (t < t_best) {
       best.ranges = n_items;
-      t_best = t;
+      t_best = on_device = t;
     }
   }
   for (int32_t s = 1; s <= 8; s *= 2) {
@@ -155,10 +166,11 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
     }
     const double fixed = f.a + (s > 1 ? f.m0 + f.m1 * s : 0.0);
     if (fixed + sum / n_cus >= t_best) continue;  // (also keeps the dealing short)
-    const double t = fixed + dealt_in_eighths(runs, cus);
-    if (1.03 * t < t_best) {
+    const double dealt = fixed + dealt_in_eighths(runs, cus), t = s > 1 ? std::max(dealt, host + kLaunch) : dealt;
+    if (1.03 * t < t_best || (t == t_best && 1.03 * dealt < on_device)) {
       best.splits = s;
       t_best = t;
+      on_device = dealt;
     }
   }
   return best;

@@ -638,7 +638,7 @@ int main(int argc, char** argv) {
   // kernel), keys per dK/dV block, launches of tiers that move their own patches
   // (embedding and de-embedding, hidden size: all the heads' channels), tile
   // ranges; -1: not looked at.
-  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1}, s2[1] = {2};
+  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1}, s111[3] = {1, 1, 1}, s2[1] = {2};
   const struct {
     const char* what;
     mssa_plan_desc d;
@@ -652,6 +652,10 @@ int main(int argc, char** argv) {
       {"small layers: two blocks, 128", make_desc(2, t12, 20, 23, 1, 1, 8, 6, 128, MSSA_BF16, 0), 2, -1},
       {"small layers: eight blocks, 64", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 64, MSSA_BF16, 0), 8, -1},
       {"small layers: eight blocks, 128", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 128, MSSA_BF16, 0), 8, -1},
+      {"short layer, streamed in place", make_desc(2, s11, 14, 21, 1, 1, 6, 3, 64, MSSA_BF16,
+       MSSA_PLAN_POOLED_HIST_RING | MSSA_PLAN_HEAD_IN_RING), 1, -1},
+      {"short layer, streamed with copies", make_desc(3, s111, 15, 20, 1, 1, 4, 4, 64, MSSA_BF16, MSSA_PLAN_POOLED_HIST_RING), 1, -1},
+      {"short layer, one pass", make_desc(2, s11, 11, 18, 1, 0, 9, 1, 64, MSSA_BF16, 0), 1, -1},
       {"one tier, long hidden", make_desc(1, s11, 14, 15, 1, 0, 0, 77, 64, MSSA_BF16, 0), -1, -1, 1},
       {"one tier, wide embedding", make_desc(1, s2, 52, 60, 1, 0, 0, 81, 64, MSSA_BF16, 0), -1, -1, 0},
       {"key blocks: one coarse stage, 64", make_desc(3, s114, 16, 24, 1, 0, 1, 256, 64, MSSA_BF16, 0), -1, 256},
