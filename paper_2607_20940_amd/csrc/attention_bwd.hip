@@ -469,10 +469,11 @@ __device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b, const f32x16& c
 // uses) goes to its tile in HBM by range-checked stores at a per-lane offset
 // fixed for the whole kernel.
 // Measured (12 heads of 128, 9360 + 3510 queries on 26910 and 12870 keys, KB = 2):
-// 2.96 - 3.2 ms, matrix cores busy 70 % of the cycles (a wave is there 91 % of
-// them: the grid's end), LDS 31 %, the clock (1.6 GHz) set by power; pairs of
-// waves sharing a SIMD, one on the matrix core and one on the softmax, handing P
-// over through LDS behind two barriers per 64 queries: 4.24 - 4.43 ms, 44 %.
+// 3.0 - 3.3 ms, matrix cores busy two thirds of the cycles (a wave is there nine
+// tenths of them: the grid's end), LDS 30 %, the clock (1.6 GHz) set by power;
+// pairs of waves sharing a SIMD, one on the matrix core and one on the softmax,
+// handing P over through LDS behind two barriers per 64 queries: 4.24 - 4.43 ms,
+// 44 %.
 // Vector, scalar and LDS instructions per MFMA: 3.5, with the pairs 6.8.
 // Whole backward of small layers with those pairs of waves, KB = 2 and KB = 1: 13
 // heads of 128, 108 queries on 489 keys and two coarser groups 40.1, 53.3 and
