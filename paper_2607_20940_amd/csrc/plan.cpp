@@ -143,11 +143,13 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
   const double share = std::max(1.0, static_cast<double>(sc.total_tiles) / ranges);  // tiles of a range
   double on_device = f.p0 + f.pr * ranges / n_cus + f.p1 * share + f.p2 * longest / share;
   double t_best = std::max(on_device, host + kLaunch);
+  bool merges = true;
   if (equal && n_items <= cus) {
     const double t = f.u0 + longest * (f.u1 + f.u2 * static_cast<double>(n_items));
     if (t < t_best) {
       best.ranges = n_items;
       t_best = on_device = t;
+      merges = false;
     }
   }
   for (int32_t s = 1; s <= 8; s *= 2) {
@@ -167,10 +169,11 @@ FwdChoice forward_choice(const Plan& p, const std::vector<std::vector<int64_t>>&
     const double fixed = f.a + (s > 1 ? f.m0 + f.m1 * s : 0.0);
     if (fixed + sum / n_cus >= t_best) continue;  // (also keeps the dealing short)
     const double dealt = fixed + dealt_in_eighths(runs, cus), t = s > 1 ? std::max(dealt, host + kLaunch) : dealt;
-    if (1.03 * t < t_best || (t == t_best && 1.03 * dealt < on_device)) {
+    if (1.03 * t < t_best || (merges && t <= t_best && 1.03 * dealt < on_device)) {
       best.splits = s;
       t_best = t;
       on_device = dealt;
+      merges = s > 1;
     }
   }
   return best;

@@ -638,7 +638,7 @@ int main(int argc, char** argv) {
   // kernel), keys per dK/dV block, launches of tiers that move their own patches
   // (embedding and de-embedding, hidden size: all the heads' channels), tile
   // ranges; -1: not looked at.
-  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1}, s111[3] = {1, 1, 1}, s2[1] = {2};
+  const int s114[3] = {1, 1, 4}, s1114[4] = {1, 1, 1, 4}, s11[2] = {1, 1}, s111[3] = {1, 1, 1}, t124[3] = {1, 2, 4}, s2[1] = {2};
   const struct {
     const char* what;
     mssa_plan_desc d;
@@ -650,6 +650,8 @@ int main(int argc, char** argv) {
        -1, -1, 256},
       {"small layers: two blocks, 64", make_desc(2, t12, 20, 23, 1, 1, 8, 6, 64, MSSA_BF16, 0), 2, -1},
       {"small layers: two blocks, 128", make_desc(2, t12, 20, 23, 1, 1, 8, 6, 128, MSSA_BF16, 0), 2, -1},
+      {"small layers: four blocks, 64", make_desc(3, t124, 9, 13, 1, 1, 30, 1, 64, MSSA_BF16, 0), 4, -1},
+      {"small layers: four blocks, 128", make_desc(3, t124, 9, 13, 1, 1, 30, 1, 128, MSSA_BF16, 0), 4, -1},
       {"small layers: eight blocks, 64", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 64, MSSA_BF16, 0), 8, -1},
       {"small layers: eight blocks, 128", make_desc(1, s11, 7, 9, 1, 1, 80, 1, 128, MSSA_BF16, 0), 8, -1},
       {"short layer, streamed in place", make_desc(2, s11, 14, 21, 1, 1, 6, 3, 64, MSSA_BF16,
